@@ -129,8 +129,15 @@ typedef struct pgcn_partition pgcn_partition;
  *   PGCN_AGG_CHUNKS_T  the same for the plans of P_i^T alone (takes precedence);
  *   PGCN_AGG_CHUNKS_NARROW  the same for the plans of rows of at most 64 floats
  *                      (takes precedence over both);
+ *   PGCN_AGG_SLICED    0 / 1: never / always plan the aggregations of rows wider than
+ *                      64 floats for the kernel of L2-resident row slices (read by
+ *                      pgcn_partition_setup; default: on matrices of at least 2^20
+ *                      non-zeros where that is faster, chunks of about 11,000 rows,
+ *                      none across the inner and boundary rows; PGCN_AGG_CHUNKS and
+ *                      PGCN_AGG_CHUNKS_T give plain plans unless this is 1);
  *   PGCN_SEGMENT       length at which long rows are split into segments,
- *                      16..1048576 (read by pgcn_partition_setup; default 512);
+ *                      16..1048576 (read by pgcn_partition_setup; default 512; at
+ *                      least twice that in sliced plans);
  *   PGCN_AGG_SLICE_F4  float4 columns per aggregation lane slice: 16, 32 or 64
  *                      (read per call; default 64);
  *   PGCN_TN_BM=128     keeps the fp32 weight-gradient GEMM in 128-row tiles

@@ -24,6 +24,8 @@
 //    blocking; C = 1 for short rows, where each gathered row is used only a
 //    few times anyway).  Chunk c adds its partial sum to the output in chunk
 //    order; the last chunk applies the row scale.
+//  * Sliced plans (below, agg_slice_kernel) cut rows and chunks smaller, so that an
+//    XCD's L2 serves nearly every load; the rest of this list is the plain kernel.
 //  * Long runs: one wave owns one work item (a row's run of non-zeros inside
 //    a chunk): G = 64 / SL lane groups take non-zeros k, k+1, ..., k+G-1, U
 //    of them per group in flight (masked at the row's end), then the groups
@@ -270,6 +272,107 @@ template <int SL, int U>
 __global__ __launch_bounds__(256) void agg_kernel(AggParams p) {
   if ((int64_t)blockIdx.x < p.long_blocks) agg_long<SL, U>(p, blockIdx.x);
   else agg_short<SL, U>(p, (int64_t)blockIdx.x - p.long_blocks);
+}
+
+// ------------------------------------------------------ L2-resident slices ---
+//
+// Plans with Plan::sliced: rows are cut into slices of kSliceF4 = 16 float4 (256
+// bytes) and chunks are small enough that a chunk's rows of one slice fit an XCD's
+// 4 MB L2; workgroup b takes slice b % S, so (dealt round robin) an XCD gathers from
+// one slice only and nearly every load hits its L2.  What bounds it is then the CU's
+// load path.  Each of the wave's four 16-lane groups owns one item, so nothing is
+// added across lanes; items are sorted by length, so the groups end together.
+// Per step a group adds 8 rows, their loads in flight together: one index load per
+// 16 rows and group, one DPP row broadcast per row.  Rows are read through a buffer
+// resource (each chunk reads one source matrix): positions past the run's end get an
+// offset outside it, which reads as zero without a branch.
+// Measured on MI355X, 256-wide rows, no dense block: Reddit-like forward (88,000
+// columns, 28.9M non-zeros) 1466 us in full 64-float4 slices and 11 chunks, 1270 us
+// here in 8; half a Reddit-like transposed 619 -> 538 us (27 TB/s of gathered rows).
+// Whole layers, dense block included: Reddit-like forward 1523 -> 1339 us, half of it
+// backward 670 -> 593 us, R-MAT of 400,000 rows forward 2050 -> 1741 us.
+// The 16 channels of an L2 interleave by 128-byte lines: where the row stride is an
+// even number of lines, one slice of every row falls on few channels (the same
+// transposed pass at a stride of 256 floats: 575 us; at 288: 538 us), so workspace
+// matrices take an odd number of lines per row.
+
+constexpr uint32_t kSliceNowhere = 0xfffff000u;          // an offset past every resource below
+
+struct SliceSrc {
+  const float *base;      // source matrix of this chunk's columns, from the launch's first column on
+  uint32_t bytes;         // bytes from base to the end of the matrix (0: rows read as zero)
+  int32_t col0;           // first column of the matrix
+  uint32_t col_bytes;     // bytes of the column-index array
+};
+
+template <int u>
+__device__ __forceinline__ uint32_t slice_bcast(uint32_t off) {     // lane u of each row of 16 lanes
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)off, 0x150 + u, 0xf, 0xf, true);
+}
+
+__global__ __launch_bounds__(256) void agg_slice_kernel(AggParams p, SliceSrc src) {
+  constexpr int G = 64 / kSliceF4;
+  typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+  const int S = p.slices;
+  const int slice = (int)(blockIdx.x % S);
+  const int lane = threadIdx.x % 64, g = lane / kSliceF4, j = lane % kSliceF4;
+  const int64_t item = ((int64_t)(blockIdx.x / S) * 4 + threadIdx.x / 64) * G + g;
+  const bool valid = item < p.n_items;
+  WorkItem it{0, 0, 0};
+  if (valid) it = p.items[item];
+  const int len = it.len;
+  int most = __builtin_amdgcn_readlane(len, 0);
+#pragma unroll
+  for (int q = 1; q < G; ++q) {
+    const int o = __builtin_amdgcn_readlane(len, kSliceF4 * q);
+    most = o > most ? o : most;
+  }
+  // the slice's first column; readfirstlane keeps the resource in scalar registers (a clamped
+  // subtraction is a vector instruction, and loads through a vector resource loop over its values)
+  const uint32_t skip = 16u * kSliceF4 * (uint32_t)slice;
+  const int left = __builtin_amdgcn_readfirstlane((int)(src.bytes > skip ? src.bytes - skip : 0u));
+  const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<char *>(reinterpret_cast<const char *>(src.base)) + skip, 0, left, 0x00027000);
+  const __amdgpu_buffer_rsrc_t cols =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t *>(p.col), 0, (int)src.col_bytes, 0x00027000);
+  const uint32_t ldb = 4u * (uint32_t)p.ld_in, lane_off = 16u * j;
+  const uint32_t first = 4u * (uint32_t)(it.begin + j);              // indices past the run are read and not used
+  agg_f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  uint32_t next = __builtin_amdgcn_raw_buffer_load_b32(cols, first, 0, 0);
+  for (int k = 0; k < most; k += 16) {
+    const uint32_t off = k + j < len ? (next - (uint32_t)src.col0) * ldb : kSliceNowhere;
+    next = __builtin_amdgcn_raw_buffer_load_b32(cols, first + 4u * (uint32_t)(k + 16), 0, 0);
+    u32x4 x[8];
+    const int left_k = most - k;                                      // 1 ..
+#define SLICE_LOAD(i, u) x[i] = __builtin_amdgcn_raw_buffer_load_b128(rows, slice_bcast<u>(off) + lane_off, 0, 0);
+#define SLICE_4(i, u) SLICE_LOAD(i, u) SLICE_LOAD(i + 1, u + 1) SLICE_LOAD(i + 2, u + 2) SLICE_LOAD(i + 3, u + 3)
+// all loads before the first use
+#define SLICE_ADD(n)                                                                          \
+  __builtin_amdgcn_sched_barrier(0);                                                          \
+  _Pragma("unroll") for (int u = 0; u < n; ++u) acc += __builtin_bit_cast(agg_f32x4, x[u]);
+    if (left_k > 4) {
+      SLICE_4(0, 0) SLICE_4(4, 4)
+      SLICE_ADD(8)
+    } else {
+      SLICE_4(0, 0)
+      SLICE_ADD(4)
+    }
+    if (left_k > 12) {
+      SLICE_4(0, 8) SLICE_4(4, 12)
+      SLICE_ADD(8)
+    } else if (left_k > 8) {
+      SLICE_4(0, 8)
+      SLICE_ADD(4)
+    }
+#undef SLICE_ADD
+#undef SLICE_4
+#undef SLICE_LOAD
+  }
+  const int cs = slice * kSliceF4 + j;
+  if (!valid || cs >= p.c4_cnt) return;
+  const float4 sum = make_float4(acc.x, acc.y, acc.z, acc.w);
+  if (it.dst >= 0) finish(p, it.dst, p.c4_off + cs, sum);
+  else *reinterpret_cast<float4 *>(p.partials + (int64_t)(-it.dst - 1) * p.ld_part + 4 * (p.c4_off + cs)) = sum;
 }
 
 // Sum the partial slots of each split row in slot order, then store.
@@ -559,6 +662,29 @@ static int col_launches(int f4, ColLaunch *out, int max_out) {
   return n;
 }
 
+// Launches of the sliced kernel over a row of f4 float4: S = 8, 4, 2 or 1 slices of kSliceF4
+// each (S divides 8, so a slice stays on its XCDs); the last slice may be partial.
+static int slice_launches(int f4, ColLaunch *out, int max_out) {
+  int n = 0, left = (f4 + kSliceF4 - 1) / kSliceF4;
+  for (int off = 0; off < f4;) {
+    int S = 8;
+    while (S > left) S /= 2;
+    if (n == max_out) return -1;
+    out[n++] = ColLaunch{off, std::min(S * kSliceF4, f4 - off), S, kSliceF4};
+    off += S * kSliceF4;
+    left -= S;
+  }
+  return n;
+}
+
+// Bytes of a source matrix of `rows` rows from float4 column c4 of its first row to its end;
+// 0 for an absent matrix, -1 where that passes the sliced kernel's 32-bit offsets.
+static int64_t slice_bytes(const float *m, int64_t rows, int64_t ld, int c4) {
+  if (!m || rows <= 0) return 0;
+  const int64_t b = rows * ld * 4;
+  return b < (int64_t)kSliceNowhere ? b - 16 * (int64_t)c4 : -1;
+}
+
 // Feature blocks of a dense-block pass over cnt float4 columns.
 static int hub_nfb(int cnt) { return (4 * cnt + 31) / 32; }
 
@@ -567,13 +693,9 @@ static int hub_nfb(int cnt) { return (4 * cnt + 31) / 32; }
 static int64_t hub_sum_rows(const Plan &plan, int64_t f) {
   int64_t n = 0;
   if (plan.hub.rows == 0) return 0;
-  ColLaunch cl[128];
-  const int ncl = col_launches((int)((f + 3) / 4), cl, 128);
-  for (int li = 0; li < ncl; ++li)
-    for (int c0 = cl[li].off; c0 < cl[li].off + cl[li].cnt; c0 += 64) {
-      const int cnt = std::min(64, cl[li].off + cl[li].cnt - c0);
-      n = std::max<int64_t>(n, (int64_t)hub_groups(plan.hub, hub_nfb(cnt)) * plan.hub.rows);
-    }
+  const int f4 = (int)((f + 3) / 4);
+  for (int c0 = 0; c0 < f4; c0 += 64)
+    n = std::max<int64_t>(n, (int64_t)hub_groups(plan.hub, hub_nfb(std::min(64, f4 - c0))) * plan.hub.rows);
   return n;
 }
 
@@ -615,9 +737,49 @@ int launch_aggregate(const AggArgs &a, hipStream_t s) {
   const int f4 = (a.f + 3) / 4;
   const int C = plan.chunks;
   if (f4 > kMaxAggF4) return set_error(PGCN_EINVAL, "aggregation: feature widths above 63,740 are not supported");
-  ColLaunch cl[128];
-  const int ncl = col_launches(f4, cl, 128);
+  // Sliced kernel where the plan is made for it, the rows fit it and both sources and the index
+  // array are within its 32-bit offsets.
+  const bool sliced = plan.sliced && slice_width_ok(a.f) && slice_bytes(a.in_lo, a.in_split, a.ld_in, 0) >= 0 &&
+                      slice_bytes(a.in_hi, plan.ncols - a.in_split, a.ld_in, 0) >= 0 &&
+                      plan.nnz < (int64_t)kSliceNowhere / 4 - 64;
+  ColLaunch cl[256];
+  const int ncl = sliced ? slice_launches(f4, cl, 256) : col_launches(f4, cl, 128);
   if (ncl < 0) return set_error(PGCN_EINVAL, "aggregation: too many column launches");
+  if (hub.rows > 0) {                      // block sums first: the rows' items add onto them
+    TraceScope ts(a.trace_kind, s);
+    HubParams hp{};
+    hp.row_ids = hub.d_row_ids;
+    hp.col_ids = hub.d_col_ids;
+    hp.bits = hub.d_bits;
+    hp.rows = hub.rows;
+    hp.ntiles = hub.cols / kHubColTile;
+    hp.in_split = a.in_split;
+    hp.in_lo = a.in_lo;
+    hp.in_hi = a.in_hi;
+    hp.ld_in = a.ld_in;
+    hp.ld_part = p.ld_part;
+    hp.part = a.partials + (size_t)plan.slots * (size_t)p.ld_part;
+    hp.img = reinterpret_cast<uint16_t *>(hp.part + (size_t)hub_sum_rows(plan, a.f) * (size_t)p.ld_part);
+    int32_t launched = 0;
+    for (int c0 = 0; c0 < f4; c0 += 64) {  // at most 64 float4 per pass
+      hp.c4_off = c0;
+      hp.c4_cnt = std::min(64, f4 - c0);
+      hp.nfb = hub_nfb(hp.c4_cnt);
+      hp.groups = hub_groups(hub, hp.nfb);
+      hp.tiles_per_group = (hp.ntiles + hp.groups - 1) / hp.groups;
+      hipLaunchKernelGGL(hub_split_kernel, dim3((unsigned)(4 * hp.ntiles)), dim3(256), 0, s, hp);
+      PGCN_HIP(hipGetLastError());
+      hipLaunchKernelGGL(hub_kernel, dim3((unsigned)(hub.rows / kHubRowTile * hp.groups * hp.nfb)), dim3(512), 0, s, hp);
+      PGCN_HIP(hipGetLastError());
+      AggParams pc = p;
+      pc.c4_off = hp.c4_off;
+      pc.c4_cnt = hp.c4_cnt;
+      hipLaunchKernelGGL(hub_combine_kernel, dim3((unsigned)((hub.rows + 3) / 4)), dim3(256), 0, s, pc, hp);
+      PGCN_HIP(hipGetLastError());
+      launched += 3;
+    }
+    ts.set_launches(launched);
+  }
   for (int li = 0; li < ncl; ++li) {
     const int S = cl[li].S, SL = cl[li].SL;
     p.c4_off = cl[li].off;
@@ -628,49 +790,26 @@ int launch_aggregate(const AggArgs &a, hipStream_t s) {
     {
       TraceScope ts(a.trace_kind, s);      // one record for the chunk launches, which run back to back
       int32_t launched = 0;
-      if (hub.rows > 0) {                  // block sums first: the rows' items add onto them
-        HubParams hp{};
-        hp.row_ids = hub.d_row_ids;
-        hp.col_ids = hub.d_col_ids;
-        hp.bits = hub.d_bits;
-        hp.rows = hub.rows;
-        hp.ntiles = hub.cols / kHubColTile;
-        hp.in_split = a.in_split;
-        hp.in_lo = a.in_lo;
-        hp.in_hi = a.in_hi;
-        hp.ld_in = a.ld_in;
-        hp.c4_off = cl[li].off;
-        hp.c4_cnt = cl[li].cnt < 64 ? cl[li].cnt : 64;
-        hp.ld_part = p.ld_part;
-        hp.part = a.partials + (size_t)plan.slots * (size_t)p.ld_part;
-        hp.img = reinterpret_cast<uint16_t *>(hp.part + (size_t)hub_sum_rows(plan, a.f) * (size_t)p.ld_part);
-        for (int c0 = cl[li].off; c0 < cl[li].off + cl[li].cnt; c0 += 64) {   // at most 64 float4 per pass
-          hp.c4_off = c0;
-          hp.c4_cnt = cl[li].off + cl[li].cnt - c0 < 64 ? cl[li].off + cl[li].cnt - c0 : 64;
-          hp.nfb = hub_nfb(hp.c4_cnt);
-          hp.groups = hub_groups(hub, hp.nfb);
-          hp.tiles_per_group = (hp.ntiles + hp.groups - 1) / hp.groups;
-          hipLaunchKernelGGL(hub_split_kernel, dim3((unsigned)(4 * hp.ntiles)), dim3(256), 0, s, hp);
-          PGCN_HIP(hipGetLastError());
-          hipLaunchKernelGGL(hub_kernel, dim3((unsigned)(hub.rows / kHubRowTile * hp.groups * hp.nfb)), dim3(512), 0,
-                             s, hp);
-          PGCN_HIP(hipGetLastError());
-          AggParams pc = p;
-          pc.c4_off = hp.c4_off;
-          pc.c4_cnt = hp.c4_cnt;
-          hipLaunchKernelGGL(hub_combine_kernel, dim3((unsigned)((hub.rows + 3) / 4)), dim3(256), 0, s, pc, hp);
-          PGCN_HIP(hipGetLastError());
-          launched += 3;
-        }
-      }
       for (int c = 0; c < C; ++c) {
         p.mode = (c == 0 ? AGG_FIRST : 0) | (c == C - 1 ? AGG_LAST : 0);
         const int64_t b = plan.chunk_items[c], e = plan.chunk_items[c + 1];
         if (e == b) continue;
         p.items = plan.d_items + b;
         p.n_items = e - b;
-        p.n_long = first_short(plan, c, threshold) - b;
-        launch_dispatch(p, SL, s);
+        if (sliced) {
+          const bool hi = plan.chunk_cols[c] >= a.in_split;
+          const float *in = hi ? a.in_hi : a.in_lo;
+          SliceSrc src{};
+          src.bytes = (uint32_t)slice_bytes(in, hi ? plan.ncols - a.in_split : a.in_split, a.ld_in, p.c4_off);
+          src.base = in ? in + 4 * p.c4_off : nullptr;
+          src.col0 = hi ? (int32_t)a.in_split : 0;
+          src.col_bytes = (uint32_t)(plan.nnz * 4);
+          const int64_t blocks = (p.n_items + 15) / 16 * S;
+          hipLaunchKernelGGL(agg_slice_kernel, dim3((unsigned)blocks), dim3(256), 0, s, p, src);
+        } else {
+          p.n_long = first_short(plan, c, threshold) - b;
+          launch_dispatch(p, SL, s);
+        }
         ++launched;
         PGCN_HIP(hipGetLastError());
       }

@@ -1,4 +1,5 @@
 // C ABI entry points of libpgcn: argument checking and kernel composition.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 
@@ -20,29 +21,54 @@ int check_part(const pgcn_partition *p, const char *fn) {
 bool aligned16(const void *q) { return ((uintptr_t)q & 15u) == 0; }
 
 int64_t ld4(int64_t f) { return (f + 3) / 4 * 4; }
-// Row stride of a workspace matrix that an aggregation gathers from: a
-// multiple of 8 floats.  A 41-float row then spans 192 bytes, three whole
-// 64-byte lines, where a 44-float stride spreads rows over 3.5 lines on
-// average (measured: the Reddit-like 41-wide aggregation 7% faster).
-int64_t ldw(int64_t f) { return (f + 7) / 8 * 8; }
+// Row stride of a workspace matrix that an aggregation gathers from: up to 64 floats, a
+// multiple of 8.  A 41-float row then spans 192 bytes, three whole 64-byte lines, where
+// a 44-float stride spreads rows over 3.5 lines on average (measured: the Reddit-like
+// 41-wide aggregation 7% faster).  Wider: an odd number of 128-byte lines, so that the
+// 256-byte slices that an XCD gathers fall on every channel of its L2 (measured: half a
+// Reddit-like transposed aggregation of 256-wide rows, stride 256 -> 288: 575 -> 538 us;
+// R-MAT 1323 -> 1199 us; uniform, 512 -> 544: 1588 -> 1445 us).
+int64_t ldw(int64_t f) { return f <= kNarrowRow ? (f + 7) / 8 * 8 : ((f + 31) / 32 | 1) * 32; }
 
-// forward: split-row partials, plus an fp32 running sum over the column chunks
-// when the caller keeps no fp32 A (bf16 path)
-size_t fwd_acc_bytes(const pgcn_partition *p, int32_t f_in, int32_t gemm_dtype) {
+// Stride of a forward workspace matrix of all n_inner + n_bd rows that is gathered from:
+// ldw's, but a multiple of 8 where the matrix so fits pgcn_layer_fwd_noalloc's scratch
+// array (the layers that fit it have to keep fitting).
+int64_t ld_rows(const pgcn_partition *p, int32_t f) {
+  const int64_t tight = ((int64_t)f + 7) / 8 * 8;
+  return (p->n_inner + p->n_bd) * tight * (int64_t)sizeof(float) <= (int64_t)PGCN_NOALLOC_SCRATCH_BYTES ? tight : ldw(f);
+}
+
+// Whether a bf16 forward without an fp32 A aggregates over one chunk straight into the bf16
+// copy, with no running sum: only a plain plan does, which a sliced one keeps as its narrow plan.
+bool one_pass(const pgcn_partition *p, const Plan &pl) {
+  return (pl.sliced ? std::max(pl.plain_chunks, p->plan_n.chunks) : pl.chunks) <= 1 && pl.hub.rows == 0;
+}
+// Plan of a layer's forward aggregation: `fp32_out` says whether the caller keeps an fp32 A.
+const Plan &fwd_plan(const pgcn_partition *p, int32_t f_in, int32_t gemm_dtype, bool fp32_out) {
   const Plan &pl = agg_plan(p, false, f_in);
-  if ((pl.chunks <= 1 && pl.hub.rows == 0) || gemm_dtype != PGCN_BF16) return 0;
+  return pl.sliced && gemm_dtype == PGCN_BF16 && !fp32_out && one_pass(p, pl) ? p->plan_n : pl;
+}
+// forward: split-row partials and block sums (of either plan that fwd_plan may pick)
+size_t fwd_part_bytes(const pgcn_partition *p, int32_t f_in) {
+  const Plan &pl = agg_plan(p, false, f_in);
+  const size_t b = aggregate_workspace(pl, f_in);
+  return align_up(pl.sliced && one_pass(p, pl) ? std::max(b, aggregate_workspace(p->plan_n, f_in)) : b, 256);
+}
+// ... plus an fp32 running sum over the column chunks when the caller keeps no fp32 A (bf16 path)
+size_t fwd_acc_bytes(const pgcn_partition *p, int32_t f_in, int32_t gemm_dtype) {
+  if (one_pass(p, agg_plan(p, false, f_in)) || gemm_dtype != PGCN_BF16) return 0;
   return align_up((size_t)p->n_inner * (size_t)ld4(f_in) * sizeof(float), 256);
 }
 // forward workspace: [aggregation partials | running sum | packed weights]
 size_t fwd_agg_bytes(const pgcn_partition *p, int32_t f_in, int32_t gemm_dtype) {
-  return align_up(aggregate_workspace(agg_plan(p, false, f_in), f_in), 256) + fwd_acc_bytes(p, f_in, gemm_dtype);
+  return fwd_part_bytes(p, f_in) + fwd_acc_bytes(p, f_in, gemm_dtype);
 }
 // symmetric normalisation, aggregate-first: the gathered rows scaled by d̃_u^{-1/2}
 size_t fwd_sym_off(const pgcn_partition *p, int32_t f_in, int32_t f_out, int32_t gemm_dtype) {
   return fwd_agg_bytes(p, f_in, gemm_dtype) + gemm_nk_workspace(f_out, f_in, gemm_dtype);
 }
 size_t fwd_ws(const pgcn_partition *p, int32_t f_in, int32_t f_out, int32_t gemm_dtype) {
-  const size_t sym = p->symmetric ? align_up((size_t)(p->n_inner + p->n_bd) * (size_t)ldw(f_in) * sizeof(float), 256)
+  const size_t sym = p->symmetric ? align_up((size_t)(p->n_inner + p->n_bd) * (size_t)ld_rows(p, f_in) * sizeof(float), 256)
                                   : 0;
   return fwd_sym_off(p, f_in, f_out, gemm_dtype) + sym;
 }
@@ -80,9 +106,8 @@ uint16_t *m16_ptr(const pgcn_partition *p, void *ws, int32_t f_in, int32_t f_out
 // f_out wide) | region R | packed weights]; region R first holds D = diag(1/d)
 // M and the transposed aggregation's partials, then (both consumed) the
 // split-K partials of the weight gradient.
-int64_t ld_y(int32_t f_out) { return ldw(f_out); }
 size_t y_bytes(const pgcn_partition *p, int32_t f_out) {
-  return align_up((size_t)(p->n_inner + p->n_bd) * (size_t)ld_y(f_out) * sizeof(float), 256);
+  return align_up((size_t)(p->n_inner + p->n_bd) * (size_t)ld_rows(p, f_out) * sizeof(float), 256);
 }
 size_t fwd_tf_agg_off(const pgcn_partition *p, int32_t f_out) { return y_bytes(p, f_out); }
 size_t fwd_tf_gemm_off(const pgcn_partition *p, int32_t f_out) {
@@ -93,7 +118,7 @@ size_t fwd_ws_tf(const pgcn_partition *p, int32_t f_in, int32_t f_out, int32_t d
 }
 size_t bwd_tf_region(const pgcn_partition *p, int32_t f_in, int32_t f_out) {
   const size_t g = gemm_workspace(Gemm::TN_MASK_SPLITK, f_in, f_out, (int32_t)(p->n_inner + p->n_bd));
-  const size_t d = align_up((size_t)p->n_inner * (size_t)ld_y(f_out) * sizeof(float), 256) +
+  const size_t d = align_up((size_t)p->n_inner * (size_t)ld_rows(p, f_out) * sizeof(float), 256) +
                    align_up(aggregate_workspace(agg_plan(p, true, f_out), f_out), 256);
   return align_up(g > d ? g : d, 256);
 }
@@ -162,7 +187,7 @@ int layer_fwd_transform(const pgcn_partition *p, const pgcn_fwd_args *a, hipStre
   const size_t need = fwd_ws_tf(p, a->f_in, a->f_out, a->gemm_dtype);
   if (!a->workspace || a->workspace_bytes < need) return set_error(PGCN_EWORKSPACE, "pgcn_layer_fwd: workspace too small");
   if (p->n_inner == 0) return PGCN_OK;
-  const int64_t ldy = ld_y(a->f_out);
+  const int64_t ldy = ld_rows(p, a->f_out);
   float *Y = (float *)a->workspace;
   const bool bd = p->n_bd > 0 && a->H_bd != nullptr;
   GemmArgs m{};
@@ -229,7 +254,7 @@ int layer_bwd_transform(const pgcn_partition *p, const pgcn_bwd_args *a, hipStre
     z.workspace_bytes = a->workspace_bytes;
     return launch_gemm(Gemm::TN_MASK_SPLITK, z, s);
   }
-  const int64_t ldt = ld_y(a->f_out);
+  const int64_t ldt = ld_rows(p, a->f_out);
   float *T = (float *)a->workspace;
   char *R = (char *)a->workspace + y_bytes(p, a->f_out);
   float *D = (float *)R;
@@ -356,7 +381,7 @@ extern "C" int pgcn_layer_fwd(const pgcn_partition *p, const pgcn_fwd_args *a, h
   const float *in_lo = a->H_in, *in_hi = p->n_bd > 0 ? a->H_bd : nullptr;
   int64_t ld_agg = a->ld_in;
   if (p->d_col_scale) {              // symmetric: the gathered rows scaled by d̃_u^{-1/2} first
-    const int64_t lds = ldw(a->f_in);
+    const int64_t lds = ld_rows(p, a->f_in);
     float *Hs = (float *)((char *)a->workspace + fwd_sym_off(p, a->f_in, a->f_out, a->gemm_dtype));
     rc = launch_mask_scale(a->H_in, a->ld_in, nullptr, 0, p->d_col_scale, p->n_inner, a->f_in, Hs, lds, s);
     if (!rc && in_hi)
@@ -368,7 +393,7 @@ extern "C" int pgcn_layer_fwd(const pgcn_partition *p, const pgcn_fwd_args *a, h
     ld_agg = lds;
   }
   AggArgs g{};
-  g.plan = &agg_plan(p, false, a->f_in);
+  g.plan = &fwd_plan(p, a->f_in, a->gemm_dtype, a->A != nullptr);
   g.col = p->d_col;
   g.in_split = p->n_inner;
   g.in_lo = in_lo;
@@ -384,7 +409,7 @@ extern "C" int pgcn_layer_fwd(const pgcn_partition *p, const pgcn_fwd_args *a, h
   g.ld_bf16 = a->ld_in;
   g.partials = (float *)a->workspace;
   if (!a->A && (g.plan->chunks > 1 || g.plan->hub.rows > 0)) {   // running sum over chunks (and the block sum)
-    g.out_lo = (float *)((char *)a->workspace + align_up(aggregate_workspace(*g.plan, a->f_in), 256));
+    g.out_lo = (float *)((char *)a->workspace + fwd_part_bytes(p, a->f_in));
     g.ld_out = ld4(a->f_in);
   }
   g.trace_kind = PGCN_TK_AGG_FWD;
@@ -543,7 +568,7 @@ int sage_fwd_transform(const pgcn_partition *p, const pgcn_sage_fwd_args *a, hip
   if (!a->workspace || a->workspace_bytes < need)
     return set_error(PGCN_EWORKSPACE, "pgcn_sage_layer_fwd: workspace too small");
   if (p->n_inner == 0) return PGCN_OK;
-  const int64_t ldy = ld_y(a->f_out);
+  const int64_t ldy = ld_rows(p, a->f_out);
   float *Y = (float *)a->workspace;
   const bool bd = p->n_bd > 0 && a->X_bd != nullptr;
   GemmArgs m{};
@@ -636,7 +661,7 @@ int sage_bwd_transform(const pgcn_partition *p, const pgcn_sage_bwd_args *a, hip
     }
     return PGCN_OK;
   }
-  const int64_t ldt = ld_y(a->f_out);
+  const int64_t ldt = ld_rows(p, a->f_out);
   float *T = (float *)a->workspace;
   char *R = (char *)a->workspace + y_bytes(p, a->f_out);
   const size_t region = bwd_tf_region(p, a->f_in, a->f_out);
@@ -780,7 +805,7 @@ extern "C" int pgcn_sage_layer_fwd(const pgcn_partition *p, const pgcn_sage_fwd_
 
   // z = P_i [X_in ; X_bd] (mean over N(v))
   AggArgs g{};
-  g.plan = &agg_plan(p, false, a->f_in);
+  g.plan = &fwd_plan(p, a->f_in, a->gemm_dtype, a->A != nullptr);
   g.col = p->d_col;
   g.in_split = p->n_inner;
   g.in_lo = a->X_in;
@@ -795,7 +820,7 @@ extern "C" int pgcn_sage_layer_fwd(const pgcn_partition *p, const pgcn_sage_fwd_
   g.ld_bf16 = a->ld_in;
   g.partials = (float *)a->workspace;
   if (!a->A && (g.plan->chunks > 1 || g.plan->hub.rows > 0)) {
-    g.out_lo = (float *)((char *)a->workspace + align_up(aggregate_workspace(*g.plan, a->f_in), 256));
+    g.out_lo = (float *)((char *)a->workspace + fwd_part_bytes(p, a->f_in));
     g.ld_out = ld4(a->f_in);
   }
   g.trace_kind = PGCN_TK_AGG_FWD;

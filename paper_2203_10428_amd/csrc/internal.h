@@ -30,7 +30,7 @@ struct SplitRow {
 };
 
 // Fixed work plan over one CSR matrix (rows of P_i or of P_i^T).  The
-// matrix columns are cut into `chunks` equal ranges; chunk c's items are
+// matrix columns are cut into `chunks` ranges (equal ones unless `sliced`); chunk c's items are
 // items[chunk_items[c] .. chunk_items[c+1]): first the segments of split rows
 // (items[.. chunk_whole[c])), then one item per other row's run, longest
 // first.  Split rows own `slots` partial slots in total, contiguous per row in
@@ -61,6 +61,10 @@ struct Plan {
   std::vector<WorkItem> items;
   std::vector<SplitRow> splits;
   std::vector<int64_t> chunk_items, chunk_whole;
+  std::vector<int64_t> chunk_cols;  // chunk c holds columns [chunk_cols[c], chunk_cols[c + 1])
+  int64_t ncols = 0, nnz = 0;   // columns of the matrix, entries of the array the items index
+  bool sliced = false;          // cut for the sliced kernel: every chunk reads one source matrix
+  int32_t plain_chunks = 1;     // chunks that a plain plan of these rows would have
   int64_t slots = 0;            // partial slots of all split rows
   WorkItem *d_items = nullptr;
   SplitRow *d_splits = nullptr;
@@ -104,11 +108,27 @@ namespace pgcn {
 // Aggregations of rows of at most this many floats use the narrow plans.
 constexpr int64_t kNarrowRow = 64;
 
-// The work plan for an aggregation of P_i (transposed: P_i^T) over rows of f floats.
+// float4 columns of one slice of the sliced aggregation kernel.
+constexpr int kSliceF4 = 16;
+
+// Whether the sliced kernel takes rows of f floats: wider than the narrow plans', and not where
+// the last slice would leave more than a quarter of all lanes idle (17 .. 23 float4: 67-wide
+// rows of a uniform graph took 102 us against 79 in the plain kernel).
+inline bool slice_width_ok(int64_t f) {
+  const int64_t f4 = (f + 3) / 4, slices = (f4 + kSliceF4 - 1) / kSliceF4;
+  return f > kNarrowRow && 3 * slices * kSliceF4 <= 4 * f4;
+}
+
+// The work plan for an aggregation of P_i (transposed: P_i^T) over rows of f floats.  A sliced
+// plan gives way to the plain one, where that is kept as the narrow plan, for rows that the
+// sliced kernel does not take or whose matrices pass its 32-bit offsets.
 inline const Plan &agg_plan(const pgcn_partition *p, bool transposed, int64_t f) {
-  const Plan &narrow = transposed ? p->plan_tn : p->plan_n;
+  const Plan &narrow = transposed ? p->plan_tn : p->plan_n, &wide = transposed ? p->plan_t : p->plan;
   if (f <= kNarrowRow && narrow.chunks > 0) return narrow;
-  return transposed ? p->plan_t : p->plan;
+  if (wide.sliced && wide.plain_chunks == narrow.chunks &&
+      (!slice_width_ok(f) || (p->n_inner > p->n_bd ? p->n_inner : p->n_bd) * (f + 64) * 4 > 0xffff0000ll))
+    return narrow;
+  return wide;
 }
 
 int set_error(int code, const std::string &msg) noexcept;

@@ -6,6 +6,7 @@
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
+#include <functional>
 #include <memory>
 #include <new>
 #include <numeric>
@@ -55,6 +56,13 @@ int exception_status(const char *fn) noexcept {
 
 int check_hip(hipError_t e, const char *what) {
   return set_error(PGCN_EHIP, std::string(what) + ": " + hipGetErrorString(e));
+}
+
+// Equal column ranges: chunk c of C holds columns [ncols c / C, ncols (c + 1) / C).
+static std::vector<int64_t> equal_cuts(int64_t ncols, int32_t C) {
+  std::vector<int64_t> cuts(C + 1);
+  for (int32_t c = 0; c <= C; ++c) cuts[c] = ncols * c / C;
+  return cuts;
 }
 
 // Number of column chunks of a CSR matrix for cache blocking: chunks of about
@@ -199,44 +207,132 @@ static void choose_hub(const std::vector<int64_t> &rowptr, const std::vector<int
   }
 }
 
-// Work plan of one aggregation.  A row whose run inside some chunk is longer
-// than `segment` is a split row: every run of it, in every chunk, is cut into
-// segments of at most `segment` non-zeros that write partial slots; the row's
+// Bounds of row r's runs: its run in chunk c is [q[c], q[c + 1]).
+static void run_bounds(const std::vector<int64_t> &rowptr, const std::vector<int32_t> &col,
+                       const std::vector<int64_t> &cuts, int64_t r, int64_t *q) {
+  const int32_t *rb = col.data() + rowptr[r], *re = col.data() + rowptr[r + 1];
+  const int32_t C = (int32_t)cuts.size() - 1;
+  q[0] = rowptr[r];
+  for (int32_t c = 1; c < C; ++c) q[c] = rowptr[r] + (std::lower_bound(rb, re, (int32_t)cuts[c]) - rb);
+  q[C] = rowptr[r + 1];
+}
+
+// Partial slots of a row with run bounds q: its segments when some run is longer than
+// `segment`, else 0.
+static int64_t row_slots(const int64_t *q, int32_t C, int64_t segment) {
+  bool split = false;
+  int64_t nseg = 0;
+  for (int32_t c = 0; c < C; ++c) {
+    const int64_t len = q[c + 1] - q[c];
+    split |= len > segment;
+    nseg += (len + segment - 1) / segment;
+  }
+  return split ? nseg : 0;
+}
+
+static int64_t plan_slots(const std::vector<int64_t> &rowptr, const std::vector<int32_t> &col, int64_t nrows,
+                          const std::vector<int64_t> &cuts, int64_t segment) {
+  std::vector<int64_t> q(cuts.size());
+  int64_t n = 0;
+  for (int64_t r = 0; r < nrows; ++r) {
+    if (rowptr[r + 1] - rowptr[r] <= segment) continue;
+    run_bounds(rowptr, col, cuts, r, q.data());
+    n += row_slots(q.data(), (int32_t)cuts.size() - 1, segment);
+  }
+  return n;
+}
+
+// Gathered rows per chunk of a sliced plan: of one 256-byte slice, 11,000 rows are 2.8
+// MB of an XCD's 4 MB L2 (MI355X, Reddit-like: forward 1300 us at 14,700 rows per chunk,
+// 1270 at 11,000, 1310 at 8,000; half of it transposed 553 us at 14,500, 538 at 9,700,
+// 543 at 7,300).
+constexpr int64_t kSliceChunkRows = 11000;
+// Rows of one slice that stay in an L2 beside the indices and outputs that pass through it.
+constexpr int64_t kSliceL2Rows = 12288;
+
+// Column cuts of a sliced plan (kernel agg_slice_kernel), empty where the plain plan is
+// the better one.  Columns [0, split) and [split, ncols) come from two matrices and are
+// cut apart; each side takes chunks of about kSliceChunkRows, while a row keeps >= 32
+// non-zeros per chunk.  Worth it (measured on MI355X) where the slices raise the share
+// of gathers that an L2 serves:
+//  * not below 2^20 non-zeros or 4,096 columns (whole 1 KB rows fit an L2 there);
+//  * the transposed plans gather from a workspace matrix whose stride spreads a slice
+//    over every L2 channel: always (R-MAT 400,000 rows, 256 wide: 1630 -> 1086 us;
+//    uniform 239,000 rows, 512 wide: 1399 -> 1380 us);
+//  * the forward plans gather from the caller's matrices, where a slice of rows of an even
+//    number of 128-byte lines falls on a few of the channels: only if the kSliceL2Rows
+//    most referenced columns of each chunk hold >= a quarter of its non-zeros (R-MAT 0.57
+//    of them: 1654 -> 1215 us; products-like 0.4: 1029 -> 935 us; uniform, 0.05 of them:
+//    1440 -> 1588 us, so not there).
+// PGCN_AGG_SLICED=0 / 1 (environment) never / always cuts so; a chunk count given by
+// PGCN_AGG_CHUNKS or PGCN_AGG_CHUNKS_T is the plain plans' (with PGCN_AGG_SLICED=1, the
+// total over both sides).
+static std::vector<int64_t> choose_slices(const std::vector<int64_t> &rowptr, const std::vector<int32_t> &col,
+                                          int64_t nrows, int64_t ncols, int64_t split, bool transposed,
+                                          int32_t plain_chunks) {
+  const char *env = std::getenv("PGCN_AGG_SLICED");
+  const bool forced = env && std::strcmp(env, "1") == 0;
+  const int64_t nnz = (int64_t)col.size();
+  if (nrows == 0 || ncols == 0 || (env && std::strcmp(env, "0") == 0)) return {};
+  const bool counted = std::getenv("PGCN_AGG_CHUNKS") || (transposed && std::getenv("PGCN_AGG_CHUNKS_T"));
+  if (!forced && (counted || nnz < (int64_t)1 << 20 || ncols <= 4096)) return {};
+  std::vector<int64_t> refs(ncols, 0);
+  for (int32_t c : col) refs[c]++;
+  const int64_t nnz_lo = std::accumulate(refs.begin(), refs.begin() + split, (int64_t)0);
+  auto side = [&](int64_t n, int64_t k) -> int64_t {       // chunks of a side of n columns, k non-zeros
+    if (n == 0) return 0;
+    if (forced && counted) return std::max<int64_t>(1, (plain_chunks * n + ncols / 2) / ncols);
+    const int64_t by_cache = (n + kSliceChunkRows / 2) / kSliceChunkRows, by_len = k / nrows / 32;
+    return std::max<int64_t>(1, std::min<int64_t>({by_cache, by_len, 16}));
+  };
+  const int64_t clo = side(split, nnz_lo), chi = side(ncols - split, nnz - nnz_lo);
+  std::vector<int64_t> cuts;
+  for (int64_t c = 0; c < clo; ++c) cuts.push_back(split * c / clo);
+  for (int64_t c = 0; c < chi; ++c) cuts.push_back(split + (ncols - split) * c / chi);
+  cuts.push_back(ncols);
+  if (forced || transposed) return cuts;
+  int64_t held = 0;
+  for (size_t c = 0; c + 1 < cuts.size(); ++c) {
+    std::vector<int64_t> part(refs.begin() + cuts[c], refs.begin() + cuts[c + 1]);
+    if ((int64_t)part.size() > kSliceL2Rows) {
+      std::nth_element(part.begin(), part.begin() + kSliceL2Rows, part.end(), std::greater<int64_t>());
+      part.resize(kSliceL2Rows);
+    }
+    held += std::accumulate(part.begin(), part.end(), (int64_t)0);
+  }
+  // every chunk more than the plain plan's moves each output row twice: the gathers it has to save
+  const int64_t moved = 2 * nrows * std::max<int64_t>(0, (int64_t)cuts.size() - 1 - plain_chunks);
+  return 4 * (held - moved) >= nnz ? cuts : std::vector<int64_t>{};
+}
+
+// Work plan of one aggregation over the column chunks `cuts`.  A row whose run inside
+// some chunk is longer than `segment` is a split row: every run of it, in every chunk, is
+// cut into segments of at most `segment` non-zeros that write partial slots; the row's
 // slots are contiguous in (chunk, segment) order, and one fix-up pass after
 // the last chunk adds them in that order, so results never depend on timing.
 // Every other row adds its run of each chunk to the output in chunk order
 // (empty runs are skipped except in the first and last chunk, which write
 // and finish the row).  Whole runs are scheduled longest first.
 static void build_plan(const std::vector<int64_t> &rowptr, const std::vector<int32_t> &col, int64_t nrows,
-                       int64_t ncols, int32_t segment, int32_t chunks, Plan &p) {
+                       const std::vector<int64_t> &cuts, int64_t segment, Plan &p) {
   p.items.clear();
   p.splits.clear();
   p.slots = 0;
-  p.chunks = chunks;
+  p.chunks = (int32_t)cuts.size() - 1;
+  p.chunk_cols = cuts;
+  p.ncols = cuts.back();
+  p.nnz = (int64_t)col.size();
   const int32_t C = p.chunks;
   p.chunk_items.assign(C + 1, 0);
   p.chunk_whole.assign(C, 0);
   // run bounds: row r's run in chunk c is [bnd[r*(C+1)+c], bnd[r*(C+1)+c+1])
   std::vector<int64_t> bnd((size_t)nrows * (C + 1));
-  for (int64_t r = 0; r < nrows; ++r) {
-    const int32_t *rb = col.data() + rowptr[r], *re = col.data() + rowptr[r + 1];
-    int64_t *q = bnd.data() + (size_t)r * (C + 1);
-    q[0] = rowptr[r];
-    for (int32_t c = 1; c < C; ++c) q[c] = rowptr[r] + (std::lower_bound(rb, re, (int32_t)(ncols * c / C)) - rb);
-    q[C] = rowptr[r + 1];
-  }
+  for (int64_t r = 0; r < nrows; ++r) run_bounds(rowptr, col, cuts, r, bnd.data() + (size_t)r * (C + 1));
   // split rows and their slot ranges
   std::vector<int64_t> cursor(nrows, -1);
   for (int64_t r = 0; r < nrows; ++r) {
-    const int64_t *q = bnd.data() + (size_t)r * (C + 1);
-    bool split = false;
-    int64_t nseg = 0;
-    for (int32_t c = 0; c < C; ++c) {
-      const int64_t len = q[c + 1] - q[c];
-      split |= len > segment;
-      nseg += (len + segment - 1) / segment;
-    }
-    if (!split) continue;
+    const int64_t nseg = row_slots(bnd.data() + (size_t)r * (C + 1), C, segment);
+    if (nseg == 0) continue;
     p.splits.push_back(SplitRow{(int32_t)r, (int32_t)p.slots, (int32_t)nseg, 0});
     cursor[r] = p.slots;
     p.slots += nseg;
@@ -563,24 +659,36 @@ extern "C" int pgcn_partition_setup(const pgcn_csr *csr, const pgcn_boundary_map
     const int32_t cn = choose_chunks(n_in, n_all, nnz, false, narrow, true);
     const int32_t ctn = choose_chunks(n_all, n_in, nnz, true, narrow, true);
     // a matrix may have a dense block on the matrix cores; every plan of it then indexes the
-    // rest, and the narrow plans use the wide plan's block (the same matrix, the same block)
-    std::vector<int64_t> rp_rest, rpt_rest;
-    choose_hub(p->rowptr, p->col, n_in, n_all, p->plan.hub, rp_rest, p->plan.col_rest);
-    choose_hub(p->rowptr_t, p->col_t, n_all, n_in, p->plan_t.hub, rpt_rest, p->plan_t.col_rest);
-    const bool hub = p->plan.hub.rows > 0, hub_t = p->plan_t.hub.rows > 0;
-    build_plan(hub ? rp_rest : p->rowptr, hub ? p->plan.col_rest : p->col, n_in, n_all, p->segment, c, p->plan);
-    build_plan(hub_t ? rpt_rest : p->rowptr_t, hub_t ? p->plan_t.col_rest : p->col_t, n_all, n_in, p->segment, ct,
-               p->plan_t);
-    p->plan_n.chunks = p->plan_tn.chunks = 0;
-    if (cn != c) {
-      build_plan(hub ? rp_rest : p->rowptr, hub ? p->plan.col_rest : p->col, n_in, n_all, p->segment, cn, p->plan_n);
-      share_hub(p->plan, p->plan_n);
-    }
-    if (ctn != ct) {
-      build_plan(hub_t ? rpt_rest : p->rowptr_t, hub_t ? p->plan_t.col_rest : p->col_t, n_all, n_in, p->segment, ctn,
-                 p->plan_tn);
-      share_hub(p->plan_t, p->plan_tn);
-    }
+    // rest, and the narrow plan uses the wide plan's block (the same matrix, the same block).
+    // Wide plan: sliced where that pays, else equal chunks.  The sliced kernel gives a row's
+    // segment to 16 lanes and takes segments twice as long at the same speed; longer still if
+    // the plan would otherwise take more partial slots than the plain one.
+    auto plans = [p, n_in](const std::vector<int64_t> &rp_all, const std::vector<int32_t> &cl_all, int64_t nrows,
+                           int64_t ncols, bool transposed, int32_t chunks, int32_t chunks_narrow, Plan &plan, Plan &nar) {
+      std::vector<int64_t> rp_rest;
+      choose_hub(rp_all, cl_all, nrows, ncols, plan.hub, rp_rest, plan.col_rest);
+      const bool hub = plan.hub.rows > 0;
+      const std::vector<int64_t> &rp = hub ? rp_rest : rp_all;
+      const std::vector<int32_t> &cl = hub ? plan.col_rest : cl_all;
+      const std::vector<int64_t> plain = equal_cuts(ncols, chunks),
+                                 cuts = choose_slices(rp, cl, nrows, ncols, n_in, transposed, chunks);
+      plan.sliced = !cuts.empty();
+      plan.plain_chunks = chunks;
+      int64_t segment = p->segment;
+      if (plan.sliced) {
+        const int64_t most = plan_slots(rp, cl, nrows, plain, segment);
+        segment *= 2;
+        while (plan_slots(rp, cl, nrows, cuts, segment) > most) segment *= 2;
+      }
+      build_plan(rp, cl, nrows, plan.sliced ? cuts : plain, segment, plan);
+      nar.chunks = 0;
+      if (chunks_narrow != chunks || plan.sliced) {
+        build_plan(rp, cl, nrows, equal_cuts(ncols, chunks_narrow), p->segment, nar);
+        share_hub(plan, nar);
+      }
+    };
+    plans(p->rowptr, p->col, n_in, n_all, false, c, cn, p->plan, p->plan_n);
+    plans(p->rowptr_t, p->col_t, n_all, n_in, true, ct, ctn, p->plan_t, p->plan_tn);
   }
 
   if (!p->host_only) {

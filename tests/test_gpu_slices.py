@@ -1,0 +1,120 @@
+"""The sliced aggregation kernel (PGCN_AGG_SLICED=1 takes it on any graph; large
+partitions select it by themselves) against fp64 sums and through whole layers.
+
+Element-wise bound of a row sum of d terms added in fp32 in any order, over C
+chunks and scaled by one rounded factor: (d + C + 2) 2^-24 times the sum of the
+terms' magnitudes.  Widths: a slice is 64 floats, a launch takes 8, 4, 2 or 1
+slices, so 65, 72 and 300 end in partial slices, 512 and 576 in full ones."""
+import os
+
+import numpy as np
+import pytest
+import torch
+
+from gpu_helpers import dev, host, random_partition_graph
+from oracle.partition import build_partition, propagation_matrix
+from paper_2203_10428_amd import binding as B
+from paper_2203_10428_amd.step import ld_of
+from test_gpu_hub import ENV, ENV_NARROW, FORMS, check_layer
+
+pytestmark = pytest.mark.gpu
+
+SLICED = {"PGCN_AGG_SLICED": "1"}
+U = 2.0 ** -24
+
+
+def setup(env, n_g, rowptr, col, owner, nparts, **kw):
+    old = {k: os.environ.get(k) for k in env}
+    os.environ.update(env)
+    try:
+        return B.pgcn_partition_setup(n_g, rowptr, col, owner, nparts, 0, **kw)
+    finally:
+        for k, v in old.items():
+            if v is None:
+                os.environ.pop(k, None)
+            else:
+                os.environ[k] = v
+
+
+def graph(kind):
+    n, rowptr, col, owner = random_partition_graph(700, 500, 3, 25, 9, hub_deg=600)
+    if kind == "one partition":                       # no boundary columns: one source matrix
+        return n, rowptr, col, np.zeros(n, np.int32), 1
+    if kind == "few":                                 # less than one wave of items, most rows empty
+        rowptr = np.zeros(21, np.int64)
+        rowptr[1:3] = (1, 2)
+        return 20, np.concatenate([rowptr[:3], np.full(18, 2)]), np.array([1, 0], np.int32), \
+            (np.arange(20) >= 10).astype(np.int32), 2
+    return n, rowptr, col, owner, 3
+
+
+@pytest.mark.parametrize("kind,chunks,segment", [("hubs", 1, 512), ("hubs", 5, 16), ("one partition", 2, 16),
+                                                 ("few", 1, 512)])
+@pytest.mark.parametrize("f,pad", [(65, 0), (72, 8), (128, 0), (300, 0), (512, 32), (576, 0)])
+def test_row_sums(kind, chunks, segment, f, pad):
+    n_g, rowptr, col, owner, nparts = graph(kind)
+    env = {**SLICED, "PGCN_AGG_CHUNKS": str(chunks), "PGCN_SEGMENT": str(segment)}
+    part = setup(env, n_g, rowptr, col, owner, nparts)
+    P = propagation_matrix(build_partition(n_g, rowptr, col, owner, 0, nparts), "mean")
+    info = B.pgcn_partition_info(part)
+    n, b = info["n_inner"], info["n_bd"]
+    d = np.diff(P.indptr)[:, None]
+    rng = np.random.default_rng(f)
+    X = rng.standard_normal((n + b, f)).astype(np.float32)
+    ld = ld_of(f) + pad
+
+    def mat(x):
+        t = torch.full((x.shape[0], ld), float("nan"), device="cuda")   # padding is never read as data
+        t[:, :f] = torch.from_numpy(x).cuda()
+        return t
+
+    W = torch.from_numpy(rng.standard_normal((f, 8)).astype(np.float32)).cuda()
+    for bd in (True, False):
+        nb = B.pgcn_workspace_size(part, f, 8, B.PGCN_F32)
+        A, H = torch.full((n, ld), float("nan"), device="cuda"), dev(np.zeros((n, 8)))
+        B.pgcn_layer_fwd(part, f_in=f, f_out=8, gemm_dtype=B.PGCN_F32, relu=False, ld_in=ld, ld_out=8, H_in=mat(X[:n]),
+                         H_bd=mat(X[n:]) if bd else None, W=W, A=A, A_bf16=None, H_out=H,
+                         workspace=torch.full((nb,), 255, dtype=torch.uint8, device="cuda"), workspace_bytes=nb)
+        Xd = X.astype(np.float64)
+        if not bd:
+            Xd[n:] = 0.0
+        got = host(A, f)
+        bound = (d + 2 * chunks + 4) * U * (P @ np.abs(Xd))
+        assert np.all(np.abs(got - P @ Xd) <= bound), (kind, f, bd)
+        pad4 = A[:, f:(f + 3) // 4 * 4]
+        assert torch.equal(pad4, torch.zeros_like(pad4))
+        assert torch.equal(H, H.nan_to_num(7.0))
+
+
+@pytest.mark.parametrize("model,norm,order", FORMS)
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("f_in,f_out", [(256, 256), (300, 72), (65, 100)])
+@pytest.mark.parametrize("env", [ENV, ENV_NARROW], ids=["block", "block narrow"])
+def test_layers(model, norm, order, dt, f_in, f_out, env):
+    check_layer(model, norm, order, dt, f_in, f_out, {**env, **SLICED})
+
+
+@pytest.mark.parametrize("f_in", [72, 256])
+def test_bf16_without_fp32_aggregate(f_in):
+    """One plain chunk and no dense block: no running sum is kept, so the bf16 aggregate comes
+    from the plain plan, with the workspace that it needs without slices, bit for bit."""
+    n_g, rowptr, col, owner, nparts = graph("hubs")
+    rng = np.random.default_rng(2)
+    outs, sizes = [], []
+    for env in ({"PGCN_AGG_SLICED": "0"}, SLICED):
+        part = setup(env, n_g, rowptr, col, owner, nparts)
+        info = B.pgcn_partition_info(part)
+        n, b = info["n_inner"], info["n_bd"]
+        rng = np.random.default_rng(f_in)
+        X = rng.standard_normal((n + b, f_in))
+        W = torch.from_numpy(rng.standard_normal((f_in, 64)).astype(np.float32)).cuda()
+        nb = B.pgcn_workspace_size(part, f_in, 64, B.PGCN_BF16)
+        A16 = torch.zeros((n, ld_of(f_in)), dtype=torch.bfloat16, device="cuda")
+        H = dev(np.zeros((n, 64)))
+        B.pgcn_layer_fwd(part, f_in=f_in, f_out=64, gemm_dtype=B.PGCN_BF16, relu=True, ld_in=ld_of(f_in), ld_out=64,
+                         H_in=dev(X[:n]), H_bd=dev(X[n:]), W=W, A=None, A_bf16=A16, H_out=H,
+                         workspace=torch.empty(nb, dtype=torch.uint8, device="cuda"), workspace_bytes=nb)
+        outs.append((A16, H))
+        sizes.append(nb)
+    assert sizes[0] == sizes[1] and info["spmm_chunks"] == 2
+    assert torch.equal(outs[0][0], outs[1][0]) and torch.equal(outs[0][1], outs[1][1])
