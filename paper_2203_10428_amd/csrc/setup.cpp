@@ -7,9 +7,11 @@
 #include <cstdlib>
 #include <cstring>
 #include <functional>
+#include <future>
 #include <memory>
 #include <new>
 #include <numeric>
+#include <system_error>
 #include <utility>
 
 #include "internal.h"
@@ -687,8 +689,19 @@ extern "C" int pgcn_partition_setup(const pgcn_csr *csr, const pgcn_boundary_map
         share_hub(plan, nar);
       }
     };
+    // the two sides share nothing but their inputs: P_i^T's plans on a second thread (products-like
+    // set-up 8.8 s in turn, 5.7 s so on the same CPUs)
+    auto side_t = [&] { plans(p->rowptr_t, p->col_t, n_all, n_in, true, ct, ctn, p->plan_t, p->plan_tn); };
+    std::future<void> other;
+    if (nnz >= (int64_t)1 << 16) {
+      try {
+        other = std::async(std::launch::async, side_t);
+      } catch (const std::system_error &) {            // no thread to be had: in turn, below
+      }
+    }
     plans(p->rowptr, p->col, n_in, n_all, false, c, cn, p->plan, p->plan_n);
-    plans(p->rowptr_t, p->col_t, n_all, n_in, true, ct, ctn, p->plan_t, p->plan_tn);
+    if (other.valid()) other.get();
+    else side_t();
   }
 
   if (!p->host_only) {
