@@ -389,8 +389,7 @@ __global__ __launch_bounds__(256) void agg_fixup_kernel(AggParams p, const Split
 // ------------------------------------------------------------ dense block ---
 //
 // Block sums on the matrix cores: S[r] = sum over hub columns c of bit(r, c) H[c]
-// for the hub rows r.  First hub_split_kernel (four workgroups per tile, two
-// columns per thread) writes, per tile of kHubColTile =
+// for the hub rows r.  First hub_split_kernel writes, per tile of kHubColTile =
 // 32 hub columns and per block of 32 features of this launch's float4 slice,
 // the tile's gathered rows as three bf16 parts (hi = bf16(x), mid = bf16(x -
 // hi), lo = bf16(x - hi - mid): x = hi + mid + lo exactly for normal fp32 x),
@@ -448,46 +447,48 @@ __device__ __forceinline__ uint16_t hub_bf16(float x) {
 }
 __device__ __forceinline__ float hub_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
-// Four workgroups per tile (b = 4 tile + quarter): thread (w, l) splits columns
-// 8 quarter + 2 w and + 1 of features 4 l .. 4 l + 3.
+// Four workgroups per tile (b = 4 tile + quarter), one feature of the pass per thread:
+// it reads its feature of the quarter's 8 columns (a wave reads 256 contiguous bytes of
+// each row) and writes one 16-byte vector per part.  Bound by its 12 MB of image writes at
+// 8192 columns: as 4-byte words (two columns per thread) they took 21.7 us, so 15.7; 13.1
+// and 7.9 us at 4096.
 __global__ __launch_bounds__(256) void hub_split_kernel(HubParams p) {
-  const int ct = blockIdx.x >> 2, t = threadIdx.x, lane = t & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-  const int c0 = 8 * (blockIdx.x & 3) + 2 * wave;
-  const bool f4_ok = lane < p.c4_cnt;
-  const int cb = 4 * (p.c4_off + lane);
-  float4 x2[2];
+  const int ct = blockIdx.x >> 2, c0 = 8 * (blockIdx.x & 3), f = threadIdx.x;
+  if (f >= 32 * p.nfb) return;
+  const bool ok = f < 4 * p.c4_cnt;
+  float x[8];
 #pragma unroll
-  for (int e = 0; e < 2; ++e) {
+  for (int e = 0; e < 8; ++e) {
     const int c = p.col_ids[ct * kHubColTile + c0 + e];
     const float *src = nullptr;
     if (c >= 0) {
       if (c < p.in_split) src = p.in_lo + (int64_t)c * p.ld_in;
       else if (p.in_hi) src = p.in_hi + (int64_t)(c - p.in_split) * p.ld_in;
     }
-    x2[e] = (f4_ok && src) ? *reinterpret_cast<const float4 *>(src + cb) : make_float4(0.f, 0.f, 0.f, 0.f);
+    x[e] = (ok && src) ? src[4 * p.c4_off + f] : 0.f;
   }
-  // features 4 lane .. 4 lane + 3 all sit in feature block lane / 8, rows 4 (lane % 8) .. +3
-  uint16_t *img = p.img + ((int64_t)(lane >> 3) * p.ntiles + ct) * (kHubImage / 2);
+  hub_u32x4 v[3];
 #pragma unroll
-  for (int fe = 0; fe < 4; ++fe) {
-    uint32_t v[3] = {0u, 0u, 0u};
+  for (int w = 0; w < 4; ++w) {
+    uint32_t q[3] = {0u, 0u, 0u};
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
-      const float x = fe == 0 ? x2[e].x : fe == 1 ? x2[e].y : fe == 2 ? x2[e].z : x2[e].w;
-      const uint16_t hi = hub_bf16(x);
-      const float r1 = x - hub_f32(hi);
+      const uint16_t hi = hub_bf16(x[2 * w + e]);
+      const float r1 = x[2 * w + e] - hub_f32(hi);
       const uint16_t mi = hub_bf16(r1);
       const uint16_t lo = hub_bf16(r1 - hub_f32(mi));
-      v[0] |= (uint32_t)hi << (16 * e);
-      v[1] |= (uint32_t)mi << (16 * e);
-      v[2] |= (uint32_t)lo << (16 * e);
+      q[0] |= (uint32_t)hi << (16 * e);
+      q[1] |= (uint32_t)mi << (16 * e);
+      q[2] |= (uint32_t)lo << (16 * e);
     }
-    const int fl = 4 * (lane & 7) + fe;
 #pragma unroll
-    for (int part = 0; part < 3; ++part)
-      *reinterpret_cast<uint32_t *>(img + (part * 32 + fl) * kHubLds + c0) = v[part];
+    for (int part = 0; part < 3; ++part) v[part][w] = q[part];
   }
+  // feature block f / 32, row f % 32 of the image
+  uint16_t *img = p.img + ((int64_t)(f >> 5) * p.ntiles + ct) * (kHubImage / 2);
+#pragma unroll
+  for (int part = 0; part < 3; ++part)
+    *reinterpret_cast<hub_u32x4 *>(img + (part * 32 + (f & 31)) * kHubLds + c0) = v[part];
 }
 
 // Workgroup b: row tile b / (groups nfb), column range (b / nfb) % groups, feature block b % nfb.
