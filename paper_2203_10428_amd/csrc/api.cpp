@@ -1031,7 +1031,7 @@ extern "C" int pgcn_pack_boundary(const pgcn_partition *p, int32_t kind, const f
   PGCN_REQUIRE(cols >= 0 && ld >= cols && ld % 4 == 0, "pgcn_pack_boundary: bad shape or stride");
   if (p->n_send == 0 || cols == 0) return PGCN_OK;
   PGCN_REQUIRE(src && dst && aligned16(src) && aligned16(dst), "pgcn_pack_boundary: null or unaligned buffer");
-  if (kind == PGCN_PACK_FEAT) return launch_pack(p->d_send_idx, p->n_send, src, dst, cols, ld, s);
+  if (kind == PGCN_PACK_FEAT) return launch_pack(p->d_send_idx, p->n_send, p->d_inv_ptr, p->d_inv_k, p->n_inner, src, dst, cols, ld, s);
   return launch_accum(p->d_inv_ptr, p->d_inv_k, p->n_inner, src, dst, cols, ld, s);
 } catch (...) {
   return exception_status("pgcn_pack_boundary");
