@@ -365,55 +365,80 @@ __global__ __launch_bounds__(256, 4) void gemm_nk_f32(NKParams p) {
 // bits), so the result carries fp32 accuracy.  Six v_mfma_f32_32x32x16_bf16 per 16
 // values of k take 192 matrix-core cycles, against 512 for the eight
 // v_mfma_f32_32x32x2f32 of the plain fp32 kernel.  The weights arrive already
-// split (pack_b_split_kernel); the activations are split once per workgroup
-// while staged.  Slabs of 16 values of k: per operand three bf16 planes of
-// 32-byte rows (two 16-byte groups, the second group first in rows 8 .. 15 of
-// every 16 so that the 16 lanes of one 16-byte access pass fall on distinct
-// banks), double buffered: 48 KB and three workgroups per CU for 128 x 128
-// tiles, 72 KB and two for 128 x 256 (64 x 128 per wave: 48 matrix-core
-// instructions per slab and wave, half the split work per instruction).  Lane
-// half h takes k = 8h .. 8h + 7 of the slab on both operands.
+// split (pack_b_split_kernel).  Slabs of 16 values of k, lane half h taking 8h .. 8h + 7.
+// The weights' slab sits in LDS as three bf16 planes of 32-byte rows (two 16-byte groups,
+// the second group first in rows 8 .. 15 of every 16 so that the 16 lanes of one
+// 16-byte access pass fall on distinct banks), the activations' as fp32: a wave owns 32
+// rows and all BN columns, so each activation is split once, by the lane that
+// multiplies it, in registers.  Both double buffered: 64 KB and two workgroups per CU
+// for 128 x 256 tiles, 40 KB and three for 128 x 128.
+// What bounds it at large M is the matrix cores: 1.0 PFLOP/s of bf16 products on the
+// Yelp-like feature gradient, where a plain library bf16 product of 8192^3 reaches 1.1.
+// At the smaller ones it was the activations' latency and their uncoalesced loads (a
+// row's 64 bytes on two lanes); they are now loaded two slabs ahead, a row on four
+// lanes.  Per launch, before (activation planes in LDS, 64 x 128 per wave, one slab
+// ahead) and now: 58,000 x 256 x 256 81 -> 78 us, 239,000 x 512 x 512 masked 792 -> 743,
+// 116,000 x 112 x 112 masked 51 -> 44; 14,500 x 256 x 256 43 -> 38.
 
 __device__ __forceinline__ int nk_sw2(int row, int g) { return g ^ ((row >> 3) & 1); }
 
 template <int BM, int BN, int AK, int EK>
 __global__ __launch_bounds__(256, BN == 256 ? 2 : 3) void gemm_nk_f32s(NKParams p) {
   constexpr int BK = 16;
-  constexpr int WM = BM / 2, WN = BN / 2, TM = WM / 32, TN = WN / 32;
-  constexpr int PA = BM * BK, PB = BN * BK;             // bf16 elements of one plane
+  constexpr int TN = BN / 32;                          // each wave: 32 rows x BN columns
+  constexpr int PA = BM * BK, PB = BN * BK;            // floats of an A slab, bf16 elements of one weight plane
   constexpr int NB = 3 * BN * 2;                       // 16-byte vectors of the three weight planes
   constexpr int VB = (NB + 255) / 256;
-  static_assert(BM == 128, "one 8-value vector of A per thread");
-  constexpr int SMB = 2 * 3 * (PA + PB) * 2;
+  constexpr bool MASK = AK == NK_A_MASK;
+  static_assert(BM == 128, "four waves of 32 rows, two 16-byte vectors of A per thread");
+  constexpr int SMB = 2 * PA * 4 + 2 * 3 * PB * 2;
   constexpr int SM = SMB > kNkStageFloats * 4 ? SMB : kNkStageFloats * 4;
   __shared__ __attribute__((aligned(16))) unsigned char smem[SM];
-  uint16_t *As = reinterpret_cast<uint16_t *>(smem);   // [2][3][PA]
-  uint16_t *Bs = As + 2 * 3 * PA;                      // [2][3][PB]
+  float *As = reinterpret_cast<float *>(smem);         // [2][PA]
+  uint16_t *Bs = reinterpret_cast<uint16_t *>(As + 2 * PA);   // [2][3][PB]
 
   const int t = threadIdx.x, lane = t % 64, wave = __builtin_amdgcn_readfirstlane(t / 64);
   const int tile = nk_xcd_remap(blockIdx.x, gridDim.x);
-  const int m0 = (tile / p.tiles_n) * BM, n0 = (tile % p.tiles_n) * BN;
-  const int wm0 = (wave / 2) * WM, wn0 = (wave % 2) * WN;
+  const int m0 = (tile / p.tiles_n) * BM, n0 = (tile % p.tiles_n) * BN, wm0 = 32 * wave;
+  const int h = lane >> 5, r = lane & 31;
   const uint16_t *Bp = reinterpret_cast<const uint16_t *>(p.B);
 
-  // raw loads only; the row tail, the ReLU mask and the split are applied in
-  // store(), after the MFMAs that hide the loads
-  const int am = t / 2, ag = t % 2;                    // A: row am, values 8 ag .. 8 ag + 7 of the slab
-  f32x4 rx[2], rh[AK == NK_A_MASK ? 2 : 1];
-  u32x4 rb[VB];
-  int kl = 0;
-  auto load = [&](int kt) __attribute__((always_inline)) {
-    kl = kt;
-    const int gm = m0 + am, gk = kt + 8 * ag;
-    const bool ok = gm < p.M && gk < p.K, ok1 = ok && gk + 4 < p.K;   // ld is a multiple of 4
-    const float *row = p.A + (int64_t)gm * p.lda + gk;
-    rx[0] = ok ? *reinterpret_cast<const f32x4 *>(row) : f32x4{0.f, 0.f, 0.f, 0.f};
-    rx[1] = ok1 ? *reinterpret_cast<const f32x4 *>(row + 4) : f32x4{0.f, 0.f, 0.f, 0.f};
-    if constexpr (AK == NK_A_MASK) {
-      const float *hrow = p.Am + (int64_t)gm * p.ldam + gk;
-      rh[0] = (ok && p.Am) ? *reinterpret_cast<const f32x4 *>(hrow) : f32x4{1.f, 1.f, 1.f, 1.f};
-      rh[1] = (ok1 && p.Am) ? *reinterpret_cast<const f32x4 *>(hrow + 4) : f32x4{1.f, 1.f, 1.f, 1.f};
+  // A: raw loads (a row's 64 bytes on four lanes); rows past M repeat the last one (their results
+  // are not stored), vectors past K repeat the row's last one and are zeroed when stored
+  struct Raw {
+    f32x4 x[2], m[MASK ? 2 : 1];
+  };
+  const int am = t / 4, ak = 4 * (t % 4), klast = (p.K - 1) & ~3;
+  const float *arow[2], *hrow[2];
+#pragma unroll
+  for (int v = 0; v < 2; ++v) {
+    const int64_t gm = m0 + am + 64 * v < p.M ? m0 + am + 64 * v : p.M - 1;
+    arow[v] = p.A + gm * p.lda;
+    hrow[v] = MASK && p.Am ? p.Am + gm * p.ldam : nullptr;
+  }
+  auto load_a = [&](Raw &R, int kt) __attribute__((always_inline)) {
+    const int k = kt + ak < klast ? kt + ak : klast;
+#pragma unroll
+    for (int v = 0; v < 2; ++v) {
+      R.x[v] = *reinterpret_cast<const f32x4 *>(arow[v] + k);
+      if constexpr (MASK) R.m[v] = hrow[v] ? *reinterpret_cast<const f32x4 *>(hrow[v] + k) : f32x4{1.f, 1.f, 1.f, 1.f};
     }
+  };
+  auto store_a = [&](const Raw &R, int kt, int b) __attribute__((always_inline)) {
+#pragma unroll
+    for (int v = 0; v < 2; ++v) {
+      f32x4 x = R.x[v];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if constexpr (MASK) x[e] = R.m[v][e] > 0.f ? x[e] : 0.f;
+        if (kt + ak + e >= p.K) x[e] = 0.f;
+      }
+      const int m = am + 64 * v;
+      *reinterpret_cast<f32x4 *>(As + b * PA + m * BK + 4 * nk_sw(m, t % 4)) = x;
+    }
+  };
+  u32x4 rb[VB];
+  auto load_b = [&](int kt) __attribute__((always_inline)) {
 #pragma unroll
     for (int v = 0; v < VB; ++v) {
       const int idx = t + 256 * v;
@@ -423,32 +448,7 @@ __global__ __launch_bounds__(256, BN == 256 ? 2 : 3) void gemm_nk_f32s(NKParams 
       }
     }
   };
-  auto store = [&](int b) __attribute__((always_inline)) {
-    float x[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      x[q] = rx[q / 4][q % 4];
-      if constexpr (AK == NK_A_MASK) x[q] = rh[q / 4][q % 4] > 0.f ? x[q] : 0.f;
-    }
-    if (kl + BK > p.K) {                               // the last slab (uniform): zero the k >= K tail
-      const int valid = p.K - (kl + 8 * ag);
-#pragma unroll
-      for (int q = 0; q < 8; ++q)
-        if (q >= valid) x[q] = 0.f;
-    }
-    u32x4 oh, om, ol;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      uint32_t hi, mid, lo;
-      nk_split3x2(x[2 * w], x[2 * w + 1], hi, mid, lo);
-      oh[w] = hi;
-      om[w] = mid;
-      ol[w] = lo;
-    }
-    const int off = am * BK + 8 * nk_sw2(am, ag);
-    *reinterpret_cast<u32x4 *>(As + (b * 3 + 0) * PA + off) = oh;
-    *reinterpret_cast<u32x4 *>(As + (b * 3 + 1) * PA + off) = om;
-    *reinterpret_cast<u32x4 *>(As + (b * 3 + 2) * PA + off) = ol;
+  auto store_b = [&](int b) __attribute__((always_inline)) {
 #pragma unroll
     for (int v = 0; v < VB; ++v) {
       const int idx = t + 256 * v;
@@ -459,49 +459,73 @@ __global__ __launch_bounds__(256, BN == 256 ? 2 : 3) void gemm_nk_f32s(NKParams 
     }
   };
 
-  f32x16 acc[TM][TN];
+  f32x16 acc[1][TN];
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
+  for (int j = 0; j < TN; ++j) acc[0][j] = (f32x16){};
+  // slab kt from buffer cur: its successor's A is in R (loaded two slabs ahead) and goes to the
+  // other buffer with its weights (loaded one ahead)
+  auto slab = [&](Raw &R, int kt, int cur) __attribute__((always_inline)) {
+    load_b(kt + BK < p.ldb ? kt + BK : kt);            // the last slab reloads itself (never past the packed rows)
+    // lane (h, r): values 8h .. 8h + 7 of row wm0 + r, split into their three parts
+    bf16x8 a[3];
+    {
+      const int m = wm0 + r;
+      const f32x4 x0 = *reinterpret_cast<const f32x4 *>(As + cur * PA + m * BK + 4 * nk_sw(m, 2 * h));
+      const f32x4 x1 = *reinterpret_cast<const f32x4 *>(As + cur * PA + m * BK + 4 * nk_sw(m, 2 * h + 1));
+      u32x4 o[3];
 #pragma unroll
-    for (int j = 0; j < TN; ++j) acc[i][j] = (f32x16){};
-
-  const int h = lane >> 5, r = lane & 31;
-  load(0);
-  store(0);
-  __syncthreads();
-  int it = 0;
-  for (int kt = 0; kt < p.K; kt += BK, ++it) {
-    const int cur = it & 1;
-    load(kt + BK < p.K ? kt + BK : kt);                // as in gemm_nk_f32
-    bf16x8 a[3][TM], b[3][TN];
-#pragma unroll
-    for (int pl = 0; pl < 3; ++pl) {
-#pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        const int row = wm0 + i * 32 + r;
-        a[pl][i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(
-                                                  As + (cur * 3 + pl) * PA + row * BK + 8 * nk_sw2(row, h)));
+      for (int w = 0; w < 4; ++w) {
+        const f32x4 &x = w < 2 ? x0 : x1;
+        uint32_t hi, mid, lo;
+        nk_split3x2(x[2 * (w % 2)], x[2 * (w % 2) + 1], hi, mid, lo);
+        o[0][w] = hi;
+        o[1][w] = mid;
+        o[2][w] = lo;
       }
 #pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int row = wn0 + j * 32 + r;
-        b[pl][j] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(
-                                                  Bs + (cur * 3 + pl) * PB + row * BK + 8 * nk_sw2(row, h)));
-      }
+      for (int pl = 0; pl < 3; ++pl) a[pl] = __builtin_bit_cast(bf16x8, o[pl]);
     }
-    // smallest products first; the TM x TN independent blocks between dependent steps
+    // smallest products first; a block's weights are read while the block before multiplies
+    // (the barriers keep the compiler from reading all blocks ahead, which spills)
     constexpr int PW[6] = {2, 1, 0, 1, 0, 0}, PX[6] = {0, 1, 2, 0, 1, 0};   // parts of weights / activations
+    bf16x8 b[2][3];
+    auto read_b = [&](int j, bf16x8 (&bb)[3]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int u = 0; u < 6; ++u)
+      for (int pl = 0; pl < 3; ++pl)
+        bb[pl] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(
+                                                Bs + (cur * 3 + pl) * PB + (j * 32 + r) * BK + 8 * nk_sw2(j * 32 + r, h)));
+    };
+    read_b(0, b[0]);
 #pragma unroll
-      for (int i = 0; i < TM; ++i)
+    for (int j = 0; j < TN; ++j) {
+      if (j + 1 < TN) read_b(j + 1, b[(j + 1) & 1]);
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[PW[u]][j], a[PX[u]][i], acc[i][j], 0, 0, 0);
-    store(cur ^ 1);
+      for (int u = 0; u < 6; ++u)
+        acc[0][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[j & 1][PW[u]], a[PX[u]], acc[0][j], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    store_a(R, kt + BK, cur ^ 1);
+    store_b(cur ^ 1);
+    load_a(R, kt + 3 * BK);
     __syncthreads();
+  };
+  Raw R0, R1;
+  load_a(R0, 0);
+  load_b(0);
+  store_a(R0, 0, 0);
+  load_a(R1, BK);
+  load_a(R0, 2 * BK);
+  store_b(0);
+  __syncthreads();
+  // two slabs a round (a register set each).  An odd last slab follows the loop, or, where its
+  // copy of the accumulators would spill (masked operand), a slab of zeros follows it.
+  int kt = 0;
+  for (; MASK ? kt < p.K : kt + BK < p.K; kt += 2 * BK) {
+    slab(R1, kt, 0);
+    slab(R0, kt + BK, 1);
   }
-  nk_epilogue<EK, TM, TN>(p, acc, m0 + wm0, n0 + wn0, lane, reinterpret_cast<float *>(smem) + wave * 32 * kNkStageLd);
+  if (!MASK && kt < p.K) slab(R1, kt, 0);
+  nk_epilogue<EK, 1, TN>(p, acc, m0 + wm0, n0, lane, reinterpret_cast<float *>(smem) + wave * 32 * kNkStageLd);
 }
 
 // ------------------------------------------------------------------ bf16 ---
