@@ -690,11 +690,17 @@ static void nk_launch(const NKParams &p0, bool bf16, hipStream_t s) {
 
 // Tile width: 64 for narrow outputs; by parts, 256 (twice the matrix-core work
 // per staged A value and per slab) where that pads no more columns than 128.
+// The widest that still gives a tile to each of the 256 compute units, or 64: on a
+// 14,500 x 256 x 256 product (114 tiles of 256, 456 of 64) 64-wide tiles take 26 us
+// against 41, on 29,000 (227 of 256, 454 of 128) 128 take 35 as 256 do, 64 take 59.
 template <int AK, int EK>
 static void nk_launch_bn(const NKParams &p, bool bf16, hipStream_t s) {
+  const int64_t tm = ((int64_t)p.M + 127) / 128, n128 = (p.N + 127) / 128, n256 = (p.N + 255) / 256;
+  constexpr int64_t kUnits = 256;
   if (p.N <= 64) nk_launch<64, AK, EK>(p, bf16, s);
-  else if (p.bplane > 0 && (p.N + 255) / 256 * 2 == (p.N + 127) / 128) nk_launch<256, AK, EK>(p, bf16, s);
-  else nk_launch<128, AK, EK>(p, bf16, s);
+  else if (p.bplane > 0 && n256 * 2 == n128 && tm * n256 >= kUnits) nk_launch<256, AK, EK>(p, bf16, s);
+  else if (tm * n128 >= kUnits) nk_launch<128, AK, EK>(p, bf16, s);
+  else nk_launch<64, AK, EK>(p, bf16, s);
 }
 
 // kind: NN_* (forward: B(n,k) = W[k][n]) or MASK_NT_* (feature gradient:
