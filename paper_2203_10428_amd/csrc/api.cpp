@@ -200,14 +200,18 @@ int layer_fwd_transform(const pgcn_partition *p, const pgcn_fwd_args *a, hipStre
   m.ldc = ldy;
   m.workspace = (float *)((char *)a->workspace + fwd_tf_gemm_off(p, a->f_out));
   m.workspace_bytes = gemm_nk_workspace(a->f_out, a->f_in, a->gemm_dtype);
-  for (int part = 0; part < (bd ? 2 : 1); ++part) {    // symmetric: rows of Y scaled by d̃_u^{-1/2}
-    m.M = (int32_t)(part ? p->n_bd : p->n_inner);
-    m.A = part ? a->H_bd : a->H_in;
-    m.C = part ? Y + p->n_inner * ldy : Y;
-    m.rowscale = p->d_col_scale ? p->d_col_scale + (part ? p->n_inner : 0) : nullptr;
-    int rc = launch_gemm_nk(p->d_col_scale ? Gemm::NN_SRC32_ROWSCALE : Gemm::NN_SRC32_PLAIN, m, s);
-    if (rc) return rc;
+  m.M = (int32_t)p->n_inner;
+  m.A = a->H_in;
+  m.C = Y;
+  m.rowscale = p->d_col_scale;       // symmetric: rows of Y scaled by d̃_u^{-1/2}
+  if (bd) {
+    m.M2 = (int32_t)p->n_bd;
+    m.A2 = a->H_bd;
+    m.C2 = Y + p->n_inner * ldy;
+    m.rowscale2 = p->d_col_scale ? p->d_col_scale + p->n_inner : nullptr;
   }
+  int rc = launch_gemm_nk(p->d_col_scale ? Gemm::NN_SRC32_ROWSCALE : Gemm::NN_SRC32_PLAIN, m, s);
+  if (rc) return rc;
   AggArgs g{};
   g.plan = &agg_plan(p, false, a->f_out);
   g.col = p->d_col;
@@ -307,14 +311,15 @@ int layer_bwd_transform(const pgcn_partition *p, const pgcn_bwd_args *a, hipStre
   d.ldc = a->ld_in;
   d.workspace = (float *)(R + bwd_tf_region(p, a->f_in, a->f_out));
   d.workspace_bytes = gemm_nk_workspace(a->f_in, a->f_out, a->gemm_dtype);
-  for (int part = 0; part < (p->n_bd > 0 ? 2 : 1); ++part) {
-    d.M = (int32_t)(part ? p->n_bd : p->n_inner);
-    d.A = part ? T + p->n_inner * ldt : T;
-    d.C = part ? a->J_bd_out : a->J_in;
-    rc = launch_gemm_nk(Gemm::MASK_NT_PLAIN, d, s);
-    if (rc) return rc;
+  d.M = (int32_t)p->n_inner;
+  d.A = T;
+  d.C = a->J_in;
+  if (p->n_bd > 0) {
+    d.M2 = (int32_t)p->n_bd;
+    d.A2 = T + p->n_inner * ldt;
+    d.C2 = a->J_bd_out;
   }
-  return PGCN_OK;
+  return launch_gemm_nk(Gemm::MASK_NT_PLAIN, d, s);
 }
 
 }  // namespace
@@ -581,13 +586,16 @@ int sage_fwd_transform(const pgcn_partition *p, const pgcn_sage_fwd_args *a, hip
   m.ldc = ldy;
   m.workspace = (float *)((char *)a->workspace + fwd_tf_gemm_off(p, a->f_out));
   m.workspace_bytes = gemm_nk_workspace(a->f_out, a->f_in, a->gemm_dtype);
-  for (int part = 0; part < (bd ? 2 : 1); ++part) {
-    m.M = (int32_t)(part ? p->n_bd : p->n_inner);
-    m.A = part ? a->X_bd : a->X_in;
-    m.C = part ? Y + p->n_inner * ldy : Y;
-    int rc = launch_gemm_nk(Gemm::NN_SRC32_PLAIN, m, s);
-    if (rc) return rc;
+  m.M = (int32_t)p->n_inner;
+  m.A = a->X_in;
+  m.C = Y;
+  if (bd) {
+    m.M2 = (int32_t)p->n_bd;
+    m.A2 = a->X_bd;
+    m.C2 = Y + p->n_inner * ldy;
   }
+  int rc = launch_gemm_nk(Gemm::NN_SRC32_PLAIN, m, s);
+  if (rc) return rc;
   AggArgs g{};
   g.plan = &agg_plan(p, false, a->f_out);
   g.col = p->d_col;
@@ -602,7 +610,7 @@ int sage_fwd_transform(const pgcn_partition *p, const pgcn_sage_fwd_args *a, hip
   g.ld_out = a->ld_out;
   g.partials = (float *)((char *)a->workspace + fwd_tf_agg_off(p, a->f_out));
   g.trace_kind = PGCN_TK_AGG_FWD;
-  int rc = launch_aggregate(g, s);
+  rc = launch_aggregate(g, s);
   if (rc) return rc;
   GemmArgs b{};                      // the self term, accumulated onto P_i Y, then the activation
   b.M = (int32_t)p->n_inner;
@@ -767,6 +775,7 @@ int sage_bwd_transform(const pgcn_partition *p, const pgcn_sage_bwd_args *a, hip
   e.M = (int32_t)p->n_bd;
   e.A = T + p->n_inner * ldt;
   e.C = a->J_bd_out;
+  e.packed = true;
   return launch_gemm_nk(Gemm::MASK_NT_PLAIN, e, s);
 }
 

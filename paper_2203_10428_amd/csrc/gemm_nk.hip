@@ -64,6 +64,13 @@ struct NKParams {
   int64_t ldc;
   const float *rowscale;
   int vec;                 // C rows 16-byte aligned: ldc % 4 == 0 and C 16-byte aligned
+  // a second operand and result of the same widths and weights (a transform-first layer's
+  // boundary rows): row tiles from tm_lo on compute C2 = A2 B^T over M2 rows
+  int tm_lo;
+  int M2;
+  const float *A2;
+  float *C2;
+  const float *rowscale2;
   float *send;             // or null: final rows of C also written to send rows (stride ldc)
   const int64_t *send_ptr; // send rows of output row r: send_pos[send_ptr[r] .. send_ptr[r + 1])
   const int32_t *send_pos;
@@ -82,6 +89,17 @@ __device__ __forceinline__ uint16_t nk_bf16(float x) {
 __device__ __forceinline__ int nk_xcd_remap(int b, int g) {
   if (g % 8 != 0) return b;
   return (b % 8) * (g / 8) + b / 8;
+}
+
+// Row tile mt of this workgroup (uniform); the second part takes the place of the first in p.
+__device__ __forceinline__ int nk_row_tile(NKParams &p, int tile) {
+  const int mt = tile / p.tiles_n;
+  if (mt < p.tm_lo) return mt;
+  p.M = p.M2;
+  p.A = p.A2;
+  p.C = p.C2;
+  p.rowscale = p.rowscale2;
+  return mt - p.tm_lo;
 }
 
 // out[n][k] = (n < N && k < K) ? (trans ? W[k*ldw + n] : W[n*ldw + k]) : 0, for n < rows, k < ldk
@@ -267,7 +285,7 @@ __global__ __launch_bounds__(256, 4) void gemm_nk_f32(NKParams p) {
 
   const int t = threadIdx.x, lane = t % 64, wave = __builtin_amdgcn_readfirstlane(t / 64);
   const int tile = nk_xcd_remap(blockIdx.x, gridDim.x);
-  const int m0 = (tile / p.tiles_n) * BM, n0 = (tile % p.tiles_n) * BN;
+  const int m0 = nk_row_tile(p, tile) * BM, n0 = (tile % p.tiles_n) * BN;
   const int wm0 = (wave / 2) * WM, wn0 = (wave % 2) * WN;
   const float *Bp = reinterpret_cast<const float *>(p.B);
 
@@ -399,7 +417,7 @@ __global__ __launch_bounds__(256, BN == 256 ? 2 : 3) void gemm_nk_f32s(NKParams 
 
   const int t = threadIdx.x, lane = t % 64, wave = __builtin_amdgcn_readfirstlane(t / 64);
   const int tile = nk_xcd_remap(blockIdx.x, gridDim.x);
-  const int m0 = (tile / p.tiles_n) * BM, n0 = (tile % p.tiles_n) * BN, wm0 = 32 * wave;
+  const int m0 = nk_row_tile(p, tile) * BM, n0 = (tile % p.tiles_n) * BN, wm0 = 32 * wave;
   const int h = lane >> 5, r = lane & 31;
   const uint16_t *Bp = reinterpret_cast<const uint16_t *>(p.B);
 
@@ -542,7 +560,7 @@ __global__ __launch_bounds__(256, AK == NK_A_MASK ? 3 : 4) void gemm_nk_bf16(NKP
 
   const int t = threadIdx.x, lane = t % 64, wave = __builtin_amdgcn_readfirstlane(t / 64);
   const int tile = nk_xcd_remap(blockIdx.x, gridDim.x);
-  const int m0 = (tile / p.tiles_n) * BM, n0 = (tile % p.tiles_n) * BN;
+  const int m0 = nk_row_tile(p, tile) * BM, n0 = (tile % p.tiles_n) * BN;
   const int wm0 = (wave / 2) * WM, wn0 = (wave % 2) * WN;
   const uint16_t *Bp = reinterpret_cast<const uint16_t *>(p.B);
 
@@ -674,7 +692,9 @@ template <int BN, int AK, int EK>
 static void nk_launch(const NKParams &p0, bool bf16, hipStream_t s) {
   constexpr int BM = 128;
   NKParams p = p0;
-  const int tm = (p.M + BM - 1) / BM, tn = (p.N + BN - 1) / BN;
+  const int tn = (p.N + BN - 1) / BN;
+  p.tm_lo = (p.M + BM - 1) / BM;
+  const int tm = p.tm_lo + (p.M2 + BM - 1) / BM;
   p.tiles_n = tn;
   if constexpr (BN == 256) {                           // fp32 by parts only
     hipLaunchKernelGGL((gemm_nk_f32s<BM, BN, AK, EK>), dim3((unsigned)(tm * tn)), dim3(256), 0, s, p);
@@ -695,7 +715,7 @@ static void nk_launch(const NKParams &p0, bool bf16, hipStream_t s) {
 // against 41, on 29,000 (227 of 256, 454 of 128) 128 take 35 as 256 do, 64 take 59.
 template <int AK, int EK>
 static void nk_launch_bn(const NKParams &p, bool bf16, hipStream_t s) {
-  const int64_t tm = ((int64_t)p.M + 127) / 128, n128 = (p.N + 127) / 128, n256 = (p.N + 255) / 256;
+  const int64_t tm = ((int64_t)p.M + 127) / 128 + ((int64_t)p.M2 + 127) / 128, n128 = (p.N + 127) / 128, n256 = (p.N + 255) / 256;
   constexpr int64_t kUnits = 256;
   if (p.N <= 64) nk_launch<64, AK, EK>(p, bf16, s);
   else if (p.bplane > 0 && n256 * 2 == n128 && tm * n256 >= kUnits) nk_launch<256, AK, EK>(p, bf16, s);
@@ -716,7 +736,7 @@ int launch_gemm_nk(Gemm kind, const GemmArgs &g, hipStream_t s) {
                    kind == Gemm::NN_ACC_PLAIN || kind == Gemm::NN_SRC32_PLAIN || kind == Gemm::NN_SRC32_ROWSCALE ||
                    kind == Gemm::NN_SRC32_RELU;
   const bool parts = !bf16 && nk_f32_by_parts();
-  {
+  if (!g.packed) {
     TraceScope ts(PGCN_TK_GEMM_PACK, s);
     const unsigned blocks = (unsigned)(((int64_t)rows * ldk + 255) / 256);
     if (parts)
@@ -745,7 +765,16 @@ int launch_gemm_nk(Gemm kind, const GemmArgs &g, hipStream_t s) {
   p.C = g.C;
   p.ldc = g.ldc;
   p.rowscale = g.rowscale;
-  p.vec = (g.ldc % 4 == 0 && (reinterpret_cast<uintptr_t>(g.C) & 15) == 0) ? 1 : 0;
+  p.vec = (g.ldc % 4 == 0 && ((reinterpret_cast<uintptr_t>(g.C) | reinterpret_cast<uintptr_t>(g.C2)) & 15) == 0) ? 1 : 0;
+  if (g.M2 > 0) {
+    // kinds that read the fp32 operand with no mask and write without the send rows
+    if (g.send || g.Hmask || g.A16 || !g.A || !g.A2 || !g.C2 || (g.rowscale && !g.rowscale2))
+      return set_error(PGCN_EINVAL, "update GEMM: bad second part");
+    p.M2 = g.M2;
+    p.A2 = g.A2;
+    p.C2 = g.C2;
+    p.rowscale2 = g.rowscale2;
+  }
   if (g.send) {
     if (!fwd || !g.send_ptr || !g.send_pos || ((reinterpret_cast<uintptr_t>(g.send) & 15) && p.vec))
       return set_error(PGCN_EINVAL, "update GEMM: send rows need a forward kind, the send map and 16-byte alignment");
@@ -777,8 +806,14 @@ int launch_gemm_nk(Gemm kind, const GemmArgs &g, hipStream_t s) {
         else nk_launch_bn<NK_A_F32, NK_E_ROWSCALE>(p, false, s);
       }
       break;
-    case Gemm::MASK_NT_ROWSCALE: nk_launch_bn<NK_A_MASK, NK_E_ROWSCALE>(p, bf16, s); break;
-    case Gemm::MASK_NT_PLAIN: nk_launch_bn<NK_A_MASK, NK_E_PLAIN>(p, bf16, s); break;
+    case Gemm::MASK_NT_ROWSCALE:                       // fp32 without a mask: the kernel that stages none
+      if (!bf16 && !p.Am) nk_launch_bn<NK_A_F32, NK_E_ROWSCALE>(p, false, s);
+      else nk_launch_bn<NK_A_MASK, NK_E_ROWSCALE>(p, bf16, s);
+      break;
+    case Gemm::MASK_NT_PLAIN:
+      if (!bf16 && !p.Am) nk_launch_bn<NK_A_F32, NK_E_PLAIN>(p, false, s);
+      else nk_launch_bn<NK_A_MASK, NK_E_PLAIN>(p, bf16, s);
+      break;
     case Gemm::NT_SRC32_ACC_PLAIN:                     // C += A W^T, fp32 A rounded while staged on bf16
       if (!p.A) return set_error(PGCN_EINVAL, "launch_gemm_nk: NT_SRC32 needs the fp32 operand");
       p.Am = nullptr;

@@ -239,6 +239,13 @@ struct GemmArgs {
   float *send;
   const int64_t *send_ptr;
   const int32_t *send_pos;
+  // NN_SRC32_* and MASK_NT_PLAIN without a mask (launch_gemm_nk): a second product with the same
+  // weights, widths and strides in the same launch, C2 = A2 W over M2 rows (0: none)
+  int32_t M2;
+  const float *A2;
+  float *C2;
+  const float *rowscale2;
+  bool packed;             // launch_gemm_nk: g.workspace holds these weights from the launch before
 };
 int launch_gemm(Gemm kind, const GemmArgs &g, hipStream_t s);
 size_t gemm_workspace(Gemm kind, int32_t M, int32_t N, int32_t K);
