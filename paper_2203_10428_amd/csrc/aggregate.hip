@@ -67,6 +67,7 @@ struct AggParams {
   int32_t mode;           // AGG_FIRST | AGG_LAST
   int32_t accum_lo;       // rows < out_split add to the output's previous content
   int32_t relu;           // final rows are max(x, 0)
+  int32_t lo_scratch;     // out_lo only carries running sums: final rows are not written to it
   int64_t ld_in, ld_out, ld_bf16, ld_part;
   float *partials;
   float *send;            // or null: final rows [0, out_split) also to their send rows (stride ld_out)
@@ -120,7 +121,7 @@ __device__ __forceinline__ void finish(const AggParams &p, int64_t r, int c4, fl
     q.z = q.z > 0.f ? q.z : 0.f;
     q.w = q.w > 0.f ? q.w : 0.f;
   }
-  if (o) *reinterpret_cast<float4 *>(o + c) = q;
+  if (o && !(p.lo_scratch && r < p.out_split)) *reinterpret_cast<float4 *>(o + c) = q;
   if (p.send && r < p.out_split) {                     // four send slots per round, positions loaded together
     const agg_f32x4 qv = {q.x, q.y, q.z, q.w};
     const int64_t kb = p.send_ptr[r], ke = p.send_ptr[r + 1];
@@ -745,6 +746,7 @@ int launch_aggregate(const AggArgs &a, hipStream_t s) {
   p.ld_part = (a.f + 3) / 4 * 4;
   p.partials = a.partials;
   p.accum_lo = a.accum_lo;
+  p.lo_scratch = a.lo_scratch;
   p.relu = a.relu;
   p.send = a.send;
   p.send_ptr = a.send_ptr;

@@ -192,6 +192,7 @@ struct AggArgs {
   float *partials;
   int32_t trace_kind;      // PGCN_TK_AGG_FWD or PGCN_TK_AGG_BWD
   int32_t accum_lo;        // 1: rows [0, out_split) add to what out_lo holds (GraphSAGE self term)
+  int32_t lo_scratch;      // 1: out_lo only carries running sums, its final rows are not written
   int32_t relu;            // 1: the final rows are max(x, 0) (transform-first forward)
   // optional: the final rows [0, out_split) also go to the send rows that carry them:
   // send[k] for k in send_pos[send_ptr[r] .. send_ptr[r + 1]) (stride ld_out)

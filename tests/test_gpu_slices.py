@@ -94,27 +94,41 @@ def test_layers(model, norm, order, dt, f_in, f_out, env):
     check_layer(model, norm, order, dt, f_in, f_out, {**env, **SLICED})
 
 
-@pytest.mark.parametrize("f_in", [72, 256])
-def test_bf16_without_fp32_aggregate(f_in):
-    """One plain chunk and no dense block: no running sum is kept, so the bf16 aggregate comes
-    from the plain plan, with the workspace that it needs without slices, bit for bit."""
+@pytest.mark.parametrize("f_in,f_out,in_place", [(72, 64, False), (256, 256, False), (100, 104, False), (130, 132, False),
+                                                 (128, 128, True)])
+def test_bf16_without_fp32_aggregate(f_in, f_out, in_place):
+    """One plain chunk and no dense block: the plain plan keeps no running sum, and a sliced one
+    keeps it in H_out where a row of it holds one of A and H_out is no input (72 -> 64 and in
+    place: the plain plan, bit for bit).  The workspace is the plain plan's in every case."""
     n_g, rowptr, col, owner, nparts = graph("hubs")
-    rng = np.random.default_rng(2)
+    P = propagation_matrix(build_partition(n_g, rowptr, col, owner, 0, nparts), "mean")
     outs, sizes = [], []
     for env in ({"PGCN_AGG_SLICED": "0"}, SLICED):
         part = setup(env, n_g, rowptr, col, owner, nparts)
         info = B.pgcn_partition_info(part)
         n, b = info["n_inner"], info["n_bd"]
         rng = np.random.default_rng(f_in)
-        X = rng.standard_normal((n + b, f_in))
-        W = torch.from_numpy(rng.standard_normal((f_in, 64)).astype(np.float32)).cuda()
-        nb = B.pgcn_workspace_size(part, f_in, 64, B.PGCN_BF16)
+        X = rng.standard_normal((n + b, f_in)).astype(np.float32)
+        W = torch.from_numpy(rng.standard_normal((f_in, f_out)).astype(np.float32)).cuda()
+        nb = B.pgcn_workspace_size(part, f_in, f_out, B.PGCN_BF16)
         A16 = torch.zeros((n, ld_of(f_in)), dtype=torch.bfloat16, device="cuda")
-        H = dev(np.zeros((n, 64)))
-        B.pgcn_layer_fwd(part, f_in=f_in, f_out=64, gemm_dtype=B.PGCN_BF16, relu=True, ld_in=ld_of(f_in), ld_out=64,
-                         H_in=dev(X[:n]), H_bd=dev(X[n:]), W=W, A=None, A_bf16=A16, H_out=H,
+        H_in = dev(X[:n])
+        H = H_in if in_place else torch.full((n, ld_of(f_out)), 5.0, device="cuda")
+        B.pgcn_layer_fwd(part, f_in=f_in, f_out=f_out, gemm_dtype=B.PGCN_BF16, relu=True, ld_in=ld_of(f_in),
+                         ld_out=ld_of(f_out), H_in=H_in, H_bd=dev(X[n:]), W=W, A=None, A_bf16=A16, H_out=H,
                          workspace=torch.empty(nb, dtype=torch.uint8, device="cuda"), workspace_bytes=nb)
         outs.append((A16, H))
         sizes.append(nb)
     assert sizes[0] == sizes[1] and info["spmm_chunks"] == 2
-    assert torch.equal(outs[0][0], outs[1][0]) and torch.equal(outs[0][1], outs[1][1])
+    if in_place or f_out < (f_in + 3) // 4 * 4:
+        assert torch.equal(outs[0][0], outs[1][0]) and torch.equal(outs[0][1], outs[1][1])
+        return
+    assert torch.equal(outs[1][1][:, f_out:], outs[0][1][:, f_out:])        # H_out's padding is left alone
+    Xd, d = X.astype(np.float64), np.diff(P.indptr)[:, None]
+    exact, mag = P @ Xd, P @ np.abs(Xd)
+    for A16, H in outs:                                   # the row sum's fp32 bound, then one rounding to bf16
+        got = host(A16, f_in)
+        assert np.all(np.abs(got - exact) <= 2.0 ** -8 * np.abs(exact) + (d + 8) * U * mag)
+        Wb = W.bfloat16().double().cpu().numpy()
+        Zb = np.maximum(got @ Wb, 0.0)
+        assert np.all(np.abs(host(H, f_out) - Zb) <= (f_in + 2) * U * (np.abs(got) @ np.abs(Wb)))
