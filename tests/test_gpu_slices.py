@@ -86,6 +86,28 @@ def test_row_sums(kind, chunks, segment, f, pad):
         assert torch.equal(H, H.nan_to_num(7.0))
 
 
+@pytest.mark.parametrize("f", [257, 300, 380, 440, 600])
+def test_row_sums_with_the_remainder_joined(f):
+    """The plain kernel on a matrix of over 2^20 non-zeros: the last full slice of 64 float4 takes
+    the row's remainder along (600 floats: after a launch of one full slice)."""
+    n_g, rowptr, col, owner = random_partition_graph(9000, 4000, 3, 150, 31, hub_deg=3000)
+    env = {"PGCN_AGG_SLICED": "0", "PGCN_HUB": "0"}
+    part = setup(env, n_g, rowptr, col, owner, 3)
+    info = B.pgcn_partition_info(part)
+    assert info["nnz"] >= 1 << 20 and info["spmm_split_slots"] > 0
+    P = propagation_matrix(build_partition(n_g, rowptr, col, owner, 0, 3), "mean")
+    n, b = info["n_inner"], info["n_bd"]
+    X = np.random.default_rng(f).standard_normal((n + b, f)).astype(np.float32)
+    W = torch.ones((f, 8), device="cuda")
+    nb = B.pgcn_workspace_size(part, f, 8, B.PGCN_F32)
+    A = torch.full((n, ld_of(f)), float("nan"), device="cuda")
+    B.pgcn_layer_fwd(part, f_in=f, f_out=8, gemm_dtype=B.PGCN_F32, relu=False, ld_in=ld_of(f), ld_out=8, H_in=dev(X[:n]),
+                     H_bd=dev(X[n:]), W=W, A=A, A_bf16=None, H_out=dev(np.zeros((n, 8))),
+                     workspace=torch.empty(nb, dtype=torch.uint8, device="cuda"), workspace_bytes=nb)
+    Xd, d = X.astype(np.float64), np.diff(P.indptr)[:, None]
+    assert np.all(np.abs(host(A, f) - P @ Xd) <= (d + 8) * U * (P @ np.abs(Xd)))
+
+
 @pytest.mark.parametrize("model,norm,order", FORMS)
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
 @pytest.mark.parametrize("f_in,f_out", [(256, 256), (300, 72), (65, 100)])
