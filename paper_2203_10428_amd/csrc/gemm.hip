@@ -715,14 +715,18 @@ static int tn_slots(int N, bool bf16, bool a32) {
 // Splits over the nodes: tiles x splits about one round of resident
 // workgroups, at least 256 nodes per split, and tiles x splits a multiple of 8
 // when possible (XCD mapping).  Where 256 nodes per split leave compute units without
-// a workgroup, down to 32 nodes until each has one: a workgroup's slabs are a serial
-// chain of over a microsecond each (1,000 x 16 x 8: 4 splits 20.8 us, 32 splits 7.4).
+// a workgroup, down to 32 nodes until each has one or the partials reach 8 MB: a
+// workgroup's slabs are a serial chain of over a microsecond each (1,000 x 16 x 8:
+// 4 splits 20.8 us, 32 splits 7.4).
 constexpr int kUnits = 256;
 static int splitk_count(int M, int N, int K, int slots, int bm) {
   const int tiles = tn_tiles(M, N, bm);
   int s = slots / tiles;
   int max_s = (K + 255) / 256;
-  if (tiles * max_s < kUnits) max_s = std::min((K + 31) / 32, (kUnits + tiles - 1) / tiles);
+  if (tiles * max_s < kUnits) {
+    const int by_bytes = (int)(((int64_t)8 << 20) / ((int64_t)M * N * 4));
+    max_s = std::max(max_s, std::min({(K + 31) / 32, (kUnits + tiles - 1) / tiles, by_bytes}));
+  }
   if (s > max_s) s = max_s;
   if (s < 1) s = 1;
   int r = s;
