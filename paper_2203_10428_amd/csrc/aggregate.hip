@@ -313,11 +313,9 @@ __global__ __launch_bounds__(256) void agg_kernel(AggParams p) {
 // transposed pass at a stride of 256 floats: 575 us; at 288: 538 us), so workspace
 // matrices take an odd number of lines per row.
 
-constexpr uint32_t kSliceNowhere = 0xfffff000u;          // an offset past every resource below
-
 struct SliceSrc {
   const float *base;      // source matrix of this chunk's columns, from the launch's first column on
-  uint32_t bytes;         // bytes from base to the end of the matrix (0: rows read as zero)
+  uint32_t bytes;         // bytes from base to the end of the last row's columns (0: rows read as zero)
   int32_t col0;           // first column of the matrix
   uint32_t col_bytes;     // bytes of the column-index array
 };
@@ -728,14 +726,6 @@ static int slice_launches(int f4, ColLaunch *out, int max_out) {
   return n;
 }
 
-// Bytes of a source matrix of `rows` rows from float4 column c4 of its first row to its end;
-// 0 for an absent matrix, -1 where that passes the sliced kernel's 32-bit offsets.
-static int64_t slice_bytes(const float *m, int64_t rows, int64_t ld, int c4) {
-  if (!m || rows <= 0) return 0;
-  const int64_t b = rows * ld * 4;
-  return b < (int64_t)kSliceNowhere ? b - 16 * (int64_t)c4 : -1;
-}
-
 // Feature blocks of a dense-block pass over cnt float4 columns.
 static int hub_nfb(int cnt) { return (4 * cnt + 31) / 32; }
 
@@ -791,8 +781,8 @@ int launch_aggregate(const AggArgs &a, hipStream_t s) {
   if (f4 > kMaxAggF4) return set_error(PGCN_EINVAL, "aggregation: feature widths above 63,740 are not supported");
   // Sliced kernel where the plan is made for it, the rows fit it and both sources and the index
   // array are within its 32-bit offsets.
-  const bool sliced = plan.sliced && slice_width_ok(a.f) && slice_bytes(a.in_lo, a.in_split, a.ld_in, 0) >= 0 &&
-                      slice_bytes(a.in_hi, plan.ncols - a.in_split, a.ld_in, 0) >= 0 &&
+  const bool sliced = plan.sliced && slice_width_ok(a.f) && slice_bytes(a.in_lo ? a.in_split : 0, a.ld_in, f4, 0) >= 0 &&
+                      slice_bytes(a.in_hi ? plan.ncols - a.in_split : 0, a.ld_in, f4, 0) >= 0 &&
                       plan.nnz < (int64_t)kSliceNowhere / 4 - 64;
   ColLaunch cl[256];
   const int ncl = sliced ? slice_launches(f4, cl, 256) : col_launches(f4, cl, 128, plan.nnz >= (int64_t)1 << 20);
@@ -852,7 +842,7 @@ int launch_aggregate(const AggArgs &a, hipStream_t s) {
           const bool hi = plan.chunk_cols[c] >= a.in_split;
           const float *in = hi ? a.in_hi : a.in_lo;
           SliceSrc src{};
-          src.bytes = (uint32_t)slice_bytes(in, hi ? plan.ncols - a.in_split : a.in_split, a.ld_in, p.c4_off);
+          src.bytes = (uint32_t)slice_bytes(!in ? 0 : hi ? plan.ncols - a.in_split : a.in_split, a.ld_in, f4, p.c4_off);
           src.base = in ? in + 4 * p.c4_off : nullptr;
           src.col0 = hi ? (int32_t)a.in_split : 0;
           src.col_bytes = (uint32_t)(plan.nnz * 4);

@@ -111,6 +111,18 @@ constexpr int64_t kNarrowRow = 64;
 // float4 columns of one slice of the sliced aggregation kernel.
 constexpr int kSliceF4 = 16;
 
+// An offset past the end of every source matrix that the sliced kernel takes.
+constexpr uint32_t kSliceNowhere = 0xfffff000u;
+
+// Bytes of a source matrix of `rows` rows (0: absent) from float4 column c4 of its first row to
+// the end of its last row's f4 float4, which is all that a view into a wider matrix has to own;
+// -1 where the matrix passes the sliced kernel's 32-bit offsets.
+inline int64_t slice_bytes(int64_t rows, int64_t ld, int64_t f4, int64_t c4) {
+  if (rows <= 0) return 0;
+  const int64_t b = (rows - 1) * ld * 4 + 16 * f4;
+  return b < (int64_t)kSliceNowhere ? b - 16 * c4 : -1;
+}
+
 // Whether the sliced kernel takes rows of f floats: wider than the narrow plans', and not where
 // the last slice would leave more than a quarter of all lanes idle (17 .. 23 float4: 67-wide
 // rows of a uniform graph took 102 us against 79 in the plain kernel).

@@ -86,6 +86,33 @@ def test_row_sums(kind, chunks, segment, f, pad):
         assert torch.equal(H, H.nan_to_num(7.0))
 
 
+@pytest.mark.parametrize("f", [100, 257, 320])
+def test_sources_may_be_views_of_wider_matrices(f):
+    """Inputs in the last columns of [rows, ld] buffers of NaN: the last row ends with the buffer."""
+    n_g, rowptr, col, owner, nparts = graph("hubs")
+    part = setup(SLICED, n_g, rowptr, col, owner, nparts)
+    P = propagation_matrix(build_partition(n_g, rowptr, col, owner, 0, nparts), "mean")
+    info = B.pgcn_partition_info(part)
+    n, b = info["n_inner"], info["n_bd"]
+    X = np.random.default_rng(f).standard_normal((n + b, f)).astype(np.float32)
+    wide, ld = (f + 3) // 4 * 4, ld_of(f) + 200
+
+    def view(x):
+        buf = torch.full((x.shape[0], ld), float("nan"), device="cuda")
+        buf[:, ld - wide:ld - wide + f] = torch.from_numpy(x).cuda()
+        return buf, buf.data_ptr() + 4 * (ld - wide)
+
+    (keep, H_in), (keep_bd, H_bd) = view(X[:n]), view(X[n:])
+    nb = B.pgcn_workspace_size(part, f, 8, B.PGCN_F32)
+    A = torch.full((n, ld), float("nan"), device="cuda")
+    B.pgcn_layer_fwd(part, f_in=f, f_out=8, gemm_dtype=B.PGCN_F32, relu=False, ld_in=ld, ld_out=8, H_in=H_in, H_bd=H_bd,
+                     W=torch.ones((f, 8), device="cuda"), A=A, A_bf16=None, H_out=dev(np.zeros((n, 8))),
+                     workspace=torch.empty(nb, dtype=torch.uint8, device="cuda"), workspace_bytes=nb)
+    Xd, d = X.astype(np.float64), np.diff(P.indptr)[:, None]
+    assert np.all(np.abs(host(A, f) - P @ Xd) <= (d + 8) * U * (P @ np.abs(Xd)))
+    del keep, keep_bd
+
+
 @pytest.mark.parametrize("f", [257, 300, 380, 440, 600])
 def test_row_sums_with_the_remainder_joined(f):
     """The plain kernel on a matrix of over 2^20 non-zeros: the last full slice of 64 float4 takes
