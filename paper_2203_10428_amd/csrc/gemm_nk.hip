@@ -395,8 +395,13 @@ __global__ __launch_bounds__(256, 4) void gemm_nk_f32(NKParams p) {
 // At the smaller ones it was the activations' latency and their uncoalesced loads (a
 // row's 64 bytes on two lanes); they are now loaded two slabs ahead, a row on four
 // lanes.  Per launch, before (activation planes in LDS, 64 x 128 per wave, one slab
-// ahead) and now: 58,000 x 256 x 256 81 -> 78 us, 239,000 x 512 x 512 masked 792 -> 743,
-// 116,000 x 112 x 112 masked 51 -> 44; 14,500 x 256 x 256 43 -> 38.
+// ahead) and now: 58,000 x 256 x 256 81 -> 78 us, 14,500 x 256 x 256 43 -> 38.
+// One slab ahead for the masked operand, which brings two streams anyway, and for
+// 64-wide tiles: with two, the second register set costs the masked kernels a slab of
+// zeros after an odd last one (backward of 239,000 rows, 512 -> 47: planes 603 us, two
+// ahead 629, one ahead 617; 256 -> 112: 418, 427, 418), and 64-wide tiles, four
+// workgroups to a CU, lose in a partly filled second round (transform-first forward, 602 ->
+// 47: 180,000 rows 166, 205 and 163 us; 239,000 rows 224, 231 and 220).
 
 __device__ __forceinline__ int nk_sw2(int row, int g) { return g ^ ((row >> 3) & 1); }
 
@@ -408,6 +413,7 @@ __global__ __launch_bounds__(256, BN == 256 ? 2 : 3) void gemm_nk_f32s(NKParams 
   constexpr int NB = 3 * BN * 2;                       // 16-byte vectors of the three weight planes
   constexpr int VB = (NB + 255) / 256;
   constexpr bool MASK = AK == NK_A_MASK;
+  constexpr bool TWO = BN > 64 && !MASK;               // activations two slabs ahead, else one
   static_assert(BM == 128, "four waves of 32 rows, two 16-byte vectors of A per thread");
   constexpr int SMB = 2 * PA * 4 + 2 * 3 * PB * 2;
   constexpr int SM = SMB > kNkStageFloats * 4 ? SMB : kNkStageFloats * 4;
@@ -480,8 +486,8 @@ __global__ __launch_bounds__(256, BN == 256 ? 2 : 3) void gemm_nk_f32s(NKParams 
   f32x16 acc[1][TN];
 #pragma unroll
   for (int j = 0; j < TN; ++j) acc[0][j] = (f32x16){};
-  // slab kt from buffer cur: its successor's A is in R (loaded two slabs ahead) and goes to the
-  // other buffer with its weights (loaded one ahead)
+  // slab kt from buffer cur: its successor's A is in R and goes to the other buffer with its
+  // weights (loaded one slab ahead); R then takes the A of the slab after those in flight
   auto slab = [&](Raw &R, int kt, int cur) __attribute__((always_inline)) {
     load_b(kt + BK < p.ldb ? kt + BK : kt);            // the last slab reloads itself (never past the packed rows)
     // lane (h, r): values 8h .. 8h + 7 of row wm0 + r, split into their three parts
@@ -524,25 +530,31 @@ __global__ __launch_bounds__(256, BN == 256 ? 2 : 3) void gemm_nk_f32s(NKParams 
     }
     store_a(R, kt + BK, cur ^ 1);
     store_b(cur ^ 1);
-    load_a(R, kt + 3 * BK);
+    load_a(R, kt + (TWO ? 3 : 2) * BK);
     __syncthreads();
   };
-  Raw R0, R1;
+  Raw R0;
   load_a(R0, 0);
   load_b(0);
   store_a(R0, 0, 0);
-  load_a(R1, BK);
-  load_a(R0, 2 * BK);
-  store_b(0);
-  __syncthreads();
-  // two slabs a round (a register set each).  An odd last slab follows the loop, or, where its
-  // copy of the accumulators would spill (masked operand), a slab of zeros follows it.
-  int kt = 0;
-  for (; MASK ? kt < p.K : kt + BK < p.K; kt += 2 * BK) {
-    slab(R1, kt, 0);
-    slab(R0, kt + BK, 1);
+  load_a(R0, TWO ? 2 * BK : BK);
+  if constexpr (TWO) {                                 // two slabs a round, a register set each; an odd last one follows
+    Raw R1;
+    load_a(R1, BK);
+    store_b(0);
+    __syncthreads();
+    int kt = 0;
+    for (; kt + BK < p.K; kt += 2 * BK) {
+      slab(R1, kt, 0);
+      slab(R0, kt + BK, 1);
+    }
+    if (kt < p.K) slab(R1, kt, 0);
+  } else {
+    store_b(0);
+    __syncthreads();
+    int cur = 0;
+    for (int kt = 0; kt < p.K; kt += BK, cur ^= 1) slab(R0, kt, cur);
   }
-  if (!MASK && kt < p.K) slab(R1, kt, 0);
   nk_epilogue<EK, 1, TN>(p, acc, m0 + wm0, n0, lane, reinterpret_cast<float *>(smem) + wave * 32 * kNkStageLd);
 }
 
