@@ -86,20 +86,24 @@ __device__ __forceinline__ uint16_t nk_bf16(float x) {
   return (uint16_t)(b >> 16);
 }
 
-__device__ __forceinline__ int nk_xcd_remap(int b, int g) {
-  if (g % 8 != 0) return b;
-  return (b % 8) * (g / 8) + b / 8;
+// Tile of workgroup b of g.  Workgroups are dealt to the 8 XCDs in turn; consecutive tiles,
+// which share their rows of A, are given to one XCD (`any`: also where g is no multiple of 8).
+__device__ __forceinline__ int nk_xcd_remap(int b, int g, bool any) {
+  if (!any && g % 8 != 0) return b;
+  const int x = b % 8, r = g % 8;
+  return x * (g / 8) + (x < r ? x : r) + b / 8;
 }
 
-// Row tile mt of this workgroup (uniform); the second part takes the place of the first in p.
+// Row tile mt of this workgroup (uniform); the second part takes the place of the first in p
+// (selects, not a branch: 1% of a 60 us launch).
 __device__ __forceinline__ int nk_row_tile(NKParams &p, int tile) {
   const int mt = tile / p.tiles_n;
-  if (mt < p.tm_lo) return mt;
-  p.M = p.M2;
-  p.A = p.A2;
-  p.C = p.C2;
-  p.rowscale = p.rowscale2;
-  return mt - p.tm_lo;
+  const bool second = mt >= p.tm_lo;
+  p.M = second ? p.M2 : p.M;
+  p.A = second ? p.A2 : p.A;
+  p.C = second ? p.C2 : p.C;
+  p.rowscale = second ? p.rowscale2 : p.rowscale;
+  return second ? mt - p.tm_lo : mt;
 }
 
 // out[n][k] = (n < N && k < K) ? (trans ? W[k*ldw + n] : W[n*ldw + k]) : 0, for n < rows, k < ldk
@@ -284,7 +288,7 @@ __global__ __launch_bounds__(256, 4) void gemm_nk_f32(NKParams p) {
   float(*Bs)[BN * LK] = reinterpret_cast<float(*)[BN * LK]>(smem + 2 * BM * LK);
 
   const int t = threadIdx.x, lane = t % 64, wave = __builtin_amdgcn_readfirstlane(t / 64);
-  const int tile = nk_xcd_remap(blockIdx.x, gridDim.x);
+  const int tile = nk_xcd_remap(blockIdx.x, gridDim.x, BN == 64 && p.tiles_n > 1);
   const int m0 = nk_row_tile(p, tile) * BM, n0 = (tile % p.tiles_n) * BN;
   const int wm0 = (wave / 2) * WM, wn0 = (wave % 2) * WN;
   const float *Bp = reinterpret_cast<const float *>(p.B);
@@ -422,7 +426,7 @@ __global__ __launch_bounds__(256, BN == 256 ? 2 : 3) void gemm_nk_f32s(NKParams 
   uint16_t *Bs = reinterpret_cast<uint16_t *>(As + 2 * PA);   // [2][3][PB]
 
   const int t = threadIdx.x, lane = t % 64, wave = __builtin_amdgcn_readfirstlane(t / 64);
-  const int tile = nk_xcd_remap(blockIdx.x, gridDim.x);
+  const int tile = nk_xcd_remap(blockIdx.x, gridDim.x, BN == 64 && p.tiles_n > 1);
   const int m0 = nk_row_tile(p, tile) * BM, n0 = (tile % p.tiles_n) * BN, wm0 = 32 * wave;
   const int h = lane >> 5, r = lane & 31;
   const uint16_t *Bp = reinterpret_cast<const uint16_t *>(p.B);
@@ -571,7 +575,7 @@ __global__ __launch_bounds__(256, AK == NK_A_MASK ? 3 : 4) void gemm_nk_bf16(NKP
   uint16_t(*Bs)[BN * LK] = reinterpret_cast<uint16_t(*)[BN * LK]>(smem + 2 * BM * LK * 2);
 
   const int t = threadIdx.x, lane = t % 64, wave = __builtin_amdgcn_readfirstlane(t / 64);
-  const int tile = nk_xcd_remap(blockIdx.x, gridDim.x);
+  const int tile = nk_xcd_remap(blockIdx.x, gridDim.x, BN == 64 && p.tiles_n > 1);
   const int m0 = nk_row_tile(p, tile) * BM, n0 = (tile % p.tiles_n) * BN;
   const int wm0 = (wave / 2) * WM, wn0 = (wave % 2) * WN;
   const uint16_t *Bp = reinterpret_cast<const uint16_t *>(p.B);
@@ -722,16 +726,21 @@ static void nk_launch(const NKParams &p0, bool bf16, hipStream_t s) {
 
 // Tile width: 64 for narrow outputs; by parts, 256 (twice the matrix-core work
 // per staged A value and per slab) where that pads no more columns than 128.
-// The widest that still gives a tile to each of the 256 compute units, or 64: on a
-// 14,500 x 256 x 256 product (114 tiles of 256, 456 of 64) 64-wide tiles take 26 us
-// against 41, on 29,000 (227 of 256, 454 of 128) 128 take 35 as 256 do, 64 take 59.
+// Of these the widest that gives a tile to each of the 256 compute units, else 128; 64 only
+// while its tiles, too, number at most 256: then each unit's one tile is half the work, while
+// a second round of them reads A twice for nothing.  Transform-first forward in 128 and 64
+// columns, f32: 14,500 rows 256 -> 128 (114 tiles of 128) 25.2 and 23.8 us, 14,500 256 ->
+// 256 (228) 33.1 and 36.1 (256-wide tiles 43.7), 32,000 600 -> 128 (250) 50.0 and 55.5; bf16:
+// 8,000 128 -> 128 (63) 16.7 and 16.1, 14,500 256 -> 256 31.7 and 34.5.  A grid of 64-wide
+// tiles that is no multiple of 8 keeps a row's column tiles on one XCD (bf16, 6,000 rows,
+// 600 -> 128: 36.2 -> 30.7 us; 32.7 in 128 columns).
 template <int AK, int EK>
 static void nk_launch_bn(const NKParams &p, bool bf16, hipStream_t s) {
   const int64_t tm = ((int64_t)p.M + 127) / 128 + ((int64_t)p.M2 + 127) / 128, n128 = (p.N + 127) / 128, n256 = (p.N + 255) / 256;
   constexpr int64_t kUnits = 256;
   if (p.N <= 64) nk_launch<64, AK, EK>(p, bf16, s);
   else if (p.bplane > 0 && n256 * 2 == n128 && tm * n256 >= kUnits) nk_launch<256, AK, EK>(p, bf16, s);
-  else if (tm * n128 >= kUnits) nk_launch<128, AK, EK>(p, bf16, s);
+  else if (2 * tm * n128 > kUnits) nk_launch<128, AK, EK>(p, bf16, s);
   else nk_launch<64, AK, EK>(p, bf16, s);
 }
 

@@ -1,6 +1,7 @@
-"""Update GEMMs at the row counts where their tiles change: 64-wide tiles until
-128-row tiles of 128 or 256 columns number 256 (256 x 128 rows of one 128-wide
-column tile are 32,768).  The graph has no edges, so P is the identity and the
+"""Update GEMMs at the row counts where their tiles change: 64-wide tiles while
+those of 128 columns number at most 128 (128 x 128 rows of one 128-wide column
+tile are 16,384), 256-wide ones from 256 of them on (32,768 rows of 256 columns).
+The graph has no edges, so P is the identity and the
 products stand alone: Z = X W, J_in = M W^T, dW = X^T M.
 
 Element bounds against fp64 of the same (bf16: rounded) operands: K terms summed
@@ -32,8 +33,9 @@ def mat(gen, n, f, scale=1.0):
     return m
 
 
-# 32,640 rows: 255 row tiles (64-wide tiles for N <= 128, 256-wide for N = 512); 32,769: 257, the last of one row
-@pytest.mark.parametrize("n", [32640, 32769, 130])
+# 32,640 rows: 255 row tiles (128-wide tiles for N <= 256, 256-wide for N = 512); 32,769: 257, the last of one row;
+# 16,384 and 16,385: 128 and 129; 5,900: 47, so that two column tiles make a grid of 94, no multiple of 8
+@pytest.mark.parametrize("n", [32640, 32769, 130, 16384, 16385, 5900])
 @pytest.mark.parametrize("f_in,f_out", [(17, 256), (40, 128), (33, 300), (64, 512), (130, 65)])
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
 def test_products(n, f_in, f_out, dt):
