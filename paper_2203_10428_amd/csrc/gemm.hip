@@ -717,7 +717,8 @@ static int tn_slots(int N, bool bf16, bool a32) {
 // when possible (XCD mapping).  Where 256 nodes per split leave compute units without
 // a workgroup, down to 32 nodes until each has one or the partials reach 8 MB: a
 // workgroup's slabs are a serial chain of over a microsecond each (1,000 x 16 x 8:
-// 4 splits 20.8 us, 32 splits 7.4).
+// 4 splits 20.8 us, 32 splits 7.4).  An upper bound: a split is whole slabs, and the
+// splits that this leaves without nodes are not launched (tn_split).
 constexpr int kUnits = 256;
 static int splitk_count(int M, int N, int K, int slots, int bm) {
   const int tiles = tn_tiles(M, N, bm);
@@ -746,11 +747,6 @@ template <int BM, int BN>
 static void tn_launch(TNParams p, bool bf16, bool a32, bool parts, int splits, hipStream_t s) {
   p.tiles_n = (p.N + BN - 1) / BN;
   p.tiles = ((p.M + BM - 1) / BM) * p.tiles_n;
-  const int slab = bf16 ? 32 : 16;
-  int kchunk = (p.K + splits - 1) / splits;
-  kchunk = (kchunk + slab - 1) / slab * slab;
-  if (kchunk == 0) kchunk = slab;
-  p.kchunk = kchunk;
   const dim3 grid((unsigned)(p.tiles * splits));
   if (bf16 && a32) hipLaunchKernelGGL((gemm_tn_bf16<BN, true>), grid, dim3(256), 0, s, p);
   else if (bf16) hipLaunchKernelGGL((gemm_tn_bf16<BN, false>), grid, dim3(256), 0, s, p);
@@ -766,7 +762,9 @@ int launch_gemm(Gemm kind, const GemmArgs &g, hipStream_t s) {
   const bool a32 = g.k_split > 0;                      // second left matrix; fp32 left operand on both paths
   const bool parts = !bf16 && tn_f32_by_parts();
   const int bm = tn_bm(g.M, g.N, bf16);
-  const int splits = splitk_count(g.M, g.N, g.K, parts ? (bm == 256 ? 512 : 768) : tn_slots(g.N, bf16, a32), bm);
+  const auto [splits, kchunk] = tn_split(
+      g.K, tn_tiles(g.M, g.N, bm), splitk_count(g.M, g.N, g.K, parts ? (bm == 256 ? 512 : 768) : tn_slots(g.N, bf16, a32), bm),
+      bf16 ? 32 : 16);
   const size_t need = (size_t)splits * (size_t)g.M * (size_t)g.N * sizeof(float);
   if (!g.workspace || g.workspace_bytes < need)
     return set_error(PGCN_EWORKSPACE, "weight-gradient GEMM: workspace too small");
@@ -781,6 +779,7 @@ int launch_gemm(Gemm kind, const GemmArgs &g, hipStream_t s) {
   p.ldb = g.ldb;
   p.H = g.Hmask;
   p.ldh = g.ldm;
+  p.kchunk = kchunk;
   p.partials = g.workspace;
   p.A_hi = a32 ? g.A_hi : nullptr;
   p.ksplit = a32 ? (int)g.k_split : g.K;

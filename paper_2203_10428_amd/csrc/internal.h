@@ -260,6 +260,22 @@ struct GemmArgs {
   const float *rowscale2;
   bool packed;             // launch_gemm_nk: g.workspace holds these weights from the launch before
 };
+// Node ranges of the weight-gradient GEMM: `chunk` nodes (whole slabs) per split and the splits
+// that K nodes then fill, at most the `splits` asked for; tiles x splits stays a multiple of 8
+// where it was one (XCD mapping), which may leave up to 7 splits without a node.
+struct TnSplit {
+  int splits, chunk;
+};
+inline TnSplit tn_split(int K, int tiles, int splits, int slab) {
+  int chunk = (K + splits - 1) / splits;
+  chunk = (chunk + slab - 1) / slab * slab;
+  if (chunk == 0) chunk = slab;
+  int s = (K + chunk - 1) / chunk;
+  if (s < 1) s = 1;
+  if ((int64_t)tiles * splits % 8 == 0)
+    while ((int64_t)tiles * s % 8 != 0) ++s;
+  return TnSplit{s, chunk};
+}
 int launch_gemm(Gemm kind, const GemmArgs &g, hipStream_t s);
 size_t gemm_workspace(Gemm kind, int32_t M, int32_t N, int32_t K);
 // forward and feature-gradient GEMMs: weights packed into g.workspace first

@@ -1,5 +1,5 @@
-"""Host side of the sliced aggregation (no GPU): the range of memory that its
-buffer resource covers."""
+"""Host rules of the kernel launches (no GPU): the range of memory that the sliced
+aggregation's buffer resource covers, and the node splits of the weight gradient."""
 import ctypes as C
 import os
 import subprocess
@@ -32,3 +32,20 @@ def test_sliced_reads_end_with_the_last_row(probe, rows, ld, f):
         assert end == 4 * (rows - 1) * ld + 16 * f4 <= 4 * ((rows - 1) * ld + f + 3)
     assert probe.probe_slice_bytes(0, ld, f4, 0) == 0
     assert probe.probe_slice_bytes((1 << 30) // ld + 2, ld, f4, 0) == -1          # 4 GiB and more
+
+
+@pytest.mark.parametrize("slab", [16, 32])
+def test_weight_gradient_splits_hold_nodes(probe, slab):
+    """No split is launched without nodes (2,000 nodes, 56 splits asked for: 64-node chunks, 32 splits),
+    but for those that keep tiles x splits a multiple of 8 where it was one."""
+    out = (C.c_int * 2)()
+    for K in (0, 1, 15, 16, 17, 33, 1000, 2000, 2001, 14500, 239000):
+        for tiles in (1, 2, 3, 5, 8, 20):
+            for asked in (1, 3, 7, 8, 24, 56, 63, 125, 768):
+                probe.probe_tn_split(K, tiles, asked, slab, out)
+                splits, chunk = out
+                assert 1 <= splits <= asked and chunk % slab == 0 and chunk > 0 and splits * chunk >= K
+                used = max(1, -(-K // chunk))
+                assert splits == used or (tiles * asked % 8 == 0 and tiles * splits % 8 == 0 and splits - used < 8)
+    probe.probe_tn_split(2000, 1, 56, 32, out)
+    assert list(out) == [32, 64]
