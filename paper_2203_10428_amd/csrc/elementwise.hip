@@ -174,15 +174,13 @@ int launch_refill_copy(void *dst, const void *src, size_t bytes, hipStream_t s) 
   return PGCN_OK;
 }
 
-// By send slot, or by inner row where slots outnumber rows: the source is then read once
-// instead of once per slot.
 int launch_pack(const int32_t *idx, int64_t count, const int64_t *inv_ptr, const int32_t *inv_k, int64_t rows,
                 const float *src, float *dst, int32_t cols, int64_t ld, hipStream_t s) {
   const int f4 = (cols + 3) / 4;
   if (count == 0 || f4 == 0) return PGCN_OK;
   const int sh = lane_shift(f4);
   TraceScope ts(PGCN_TK_PACK, s);
-  if (count > rows)
+  if (pack_by_row(count, rows, f4, ld, dst))
     hipLaunchKernelGGL(pack_rows_kernel, dim3(row_blocks(rows, sh)), dim3(256), 0, s, inv_ptr, inv_k, rows, src, dst, f4,
                        ld, sh);
   else

@@ -299,6 +299,18 @@ int launch_adam(float *W, const float *G, const float *Gp, float *m, float *v, i
 // Device-to-device copy of `bytes` (a multiple of 16, both pointers 16-byte aligned) with
 // non-temporal loads and stores.
 int launch_refill_copy(void *dst, const void *src, size_t bytes, hipStream_t s);
+// Whether rows of f4 float4 (stride ld floats) are packed by inner row: the source is then read once
+// instead of once per send slot, but every slot is written by itself, so a 64-byte line that a slot
+// shares with its neighbour or leaves in part is written in pieces.  Time by slot over time by row
+// (MI355X, 20,000 .. 100,000 rows) at 2, 6 and 40 slots per row: whole lines 48 floats 1.42, 1.37,
+// 0.84; 80 floats 1.34, 1.49, 1.10; 144 floats 1.31, 1.55, 1.30; parts of lines 60 floats 1.05, 0.84,
+// 0.64; 100 floats 1.09, 0.85, 0.67; 264 floats 1.16, 0.94, 0.87; 300 floats 1.26, 1.12, 1.03; 520
+// floats 1.10, 1.03, 0.98; below 48 floats 0.5 to 1.1.
+inline bool pack_by_row(int64_t count, int64_t rows, int64_t f4, int64_t ld, const void *dst) {
+  if (count <= rows) return false;
+  if (f4 % 4 == 0 && ld % 16 == 0 && ((uintptr_t)dst & 63u) == 0) return f4 >= 20 || (f4 >= 12 && count <= 8 * rows);
+  return f4 >= 72 ? count <= 8 * rows : f4 >= 18 && count <= 2 * rows;
+}
 int launch_pack(const int32_t *idx, int64_t count, const int64_t *inv_ptr, const int32_t *inv_k, int64_t rows,
                 const float *src, float *dst, int32_t cols, int64_t ld, hipStream_t s);
 int launch_accum(const int64_t *inv_ptr, const int32_t *inv_k, int64_t rows, const float *src,

@@ -14,4 +14,8 @@ void probe_tn_split(int K, int tiles, int splits, int slab, int *out) {
   out[1] = r.chunk;
 }
 
+int probe_pack_by_row(int64_t count, int64_t rows, int64_t f4, int64_t ld, int64_t dst) {
+  return pgcn::pack_by_row(count, rows, f4, ld, (const void *)dst);
+}
+
 }  // extern "C"

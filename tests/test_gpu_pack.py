@@ -1,5 +1,7 @@
-"""Packing of the sent rows from both sides: by send slot, and by inner row where a
-partition sends rows more than once on average.  A copy: bit for bit."""
+"""Packing of the sent rows from both sides: by send slot, and, for rows of some width, by
+inner row where a partition sends rows more than once on average (the map of 12
+partitions: by row at 48, 80, 256 and 512 columns, and at 300, in parts of lines).  A copy:
+bit for bit."""
 import numpy as np
 import pytest
 import torch
@@ -12,7 +14,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("nparts,deg,by_row", [(2, 3, False), (12, 30, True)])
-@pytest.mark.parametrize("cols", [1, 5, 41, 256, 300])
+@pytest.mark.parametrize("cols", [1, 5, 41, 48, 80, 100, 256, 300, 512])
 def test_pack(nparts, deg, by_row, cols):
     n_g, rowptr, col, owner = random_partition_graph(901, 700, nparts, deg, 5)
     part = B.pgcn_partition_setup(n_g, rowptr, col, owner, nparts, 0)

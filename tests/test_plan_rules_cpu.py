@@ -1,5 +1,6 @@
 """Host rules of the kernel launches (no GPU): the range of memory that the sliced
-aggregation's buffer resource covers, and the node splits of the weight gradient."""
+aggregation's buffer resource covers, the node splits of the weight gradient and the
+side from which sent rows are packed."""
 import ctypes as C
 import os
 import subprocess
@@ -19,6 +20,7 @@ def probe(tmp_path_factory):
     lib = C.CDLL(out)
     lib.probe_slice_bytes.restype = _i64
     lib.probe_slice_bytes.argtypes = [_i64] * 4
+    lib.probe_pack_by_row.argtypes = [_i64] * 5
     return lib
 
 
@@ -49,3 +51,14 @@ def test_weight_gradient_splits_hold_nodes(probe, slab):
                 assert splits == used or (tiles * asked % 8 == 0 and tiles * splits % 8 == 0 and splits - used < 8)
     probe.probe_tn_split(2000, 1, 56, 32, out)
     assert list(out) == [32, 64]
+
+
+@pytest.mark.parametrize("f,ld,dst,most", [
+    (4, 8, 0, 0), (40, 40, 0, 0), (44, 48, 0, 0),        # narrow: by slot whatever the map
+    (48, 48, 0, 8), (64, 64, 0, 8), (80, 80, 0, 40), (512, 512, 0, 40),              # whole 64-byte lines
+    (64, 64, 16, 0), (100, 104, 0, 2), (264, 264, 0, 2), (300, 304, 0, 8), (512, 520, 0, 8), (512, 512, 32, 8)])
+def test_rows_packed_by_inner_row(probe, f, ld, dst, most):
+    """The most slots per row at which rows of f floats are packed by inner row (never at one or fewer)."""
+    rows = 1000
+    by_row = [r for r in (1, 2, 8, 40) if probe.probe_pack_by_row(r * rows, rows, (f + 3) // 4, ld, dst)]
+    assert by_row == [r for r in (2, 8, 40) if r <= most]
