@@ -129,17 +129,19 @@ typedef struct pgcn_partition pgcn_partition;
  *   PGCN_AGG_CHUNKS_T  the same for the plans of P_i^T alone (takes precedence);
  *   PGCN_AGG_CHUNKS_NARROW  the same for the plans of rows of at most 64 floats
  *                      (takes precedence over both);
- *   PGCN_AGG_SLICED    0 / 1: never / always plan the aggregations of rows wider than
- *                      64 floats for the kernel of L2-resident row slices (read by
+ *   PGCN_AGG_SLICED    0 / 1: never / always aggregate rows wider than 64 floats with the
+ *                      kernel of L2-resident row slices, over a plan of its own (read by
  *                      pgcn_partition_setup; default: on matrices of at least 2^20
- *                      non-zeros where that is faster, chunks of about 11,000 rows,
- *                      none across the inner and boundary rows; PGCN_AGG_CHUNKS and
- *                      PGCN_AGG_CHUNKS_T give plain plans unless this is 1);
+ *                      non-zeros, for widths, strides and alignments where that is
+ *                      faster, chunks of about 11,000 rows, none across the inner and
+ *                      boundary rows; PGCN_AGG_CHUNKS and PGCN_AGG_CHUNKS_T give plain
+ *                      plans alone unless this is 1).  Sources of 4 GiB and more always
+ *                      take the plain plan;
  *   PGCN_SEGMENT       length at which long rows are split into segments,
  *                      16..1048576 (read by pgcn_partition_setup; default 512; at
  *                      least twice that in sliced plans);
- *   PGCN_AGG_SLICE_F4  float4 columns per aggregation lane slice: 16, 32 or 64
- *                      (read per call; default 64);
+ *   PGCN_AGG_SLICE_F4  float4 columns per lane slice of the plain aggregation: 16, 32
+ *                      or 64 (read per call; default 64);
  *   PGCN_TN_BM=128     keeps the fp32 weight-gradient GEMM in 128-row tiles
  *                      (read once; default: 256-row tiles for f_in >= 384);
  *   PGCN_GEMM_F32=native  fp32 update GEMMs on the fp32 matrix cores instead of
@@ -151,9 +153,9 @@ typedef struct pgcn_partition pgcn_partition;
  *   PGCN_HUB_ROWS, PGCN_HUB_COLS  both > 0: force the block to that many rows
  *                      and columns (clamped to the matrix).
  * Chunks, segments and the dense block set the order in which a row's terms are
- * added (results stay deterministic for a given setting and row width); the
- * slice width and PGCN_TN_BM change only speed; PGCN_GEMM_F32 changes the
- * order of the GEMMs' fp32 sums within the same rounding bound. */
+ * added (results stay deterministic for a given setting, row width, stride and
+ * alignment); the slice width and PGCN_TN_BM change only speed; PGCN_GEMM_F32
+ * changes the order of the GEMMs' fp32 sums within the same rounding bound. */
 
 /* Largest layer width (f_in, f_out) the layer entry points accept: the
  * aggregation covers a row in at most 32 launches of up to 512 float4
@@ -172,8 +174,10 @@ typedef struct {
   int32_t nparts;
   int32_t self;
   int32_t host_only;       /* 1 if built with PGCN_SETUP_HOST_ONLY            */
-  int32_t spmm_segment;    /* rows longer than this are split (fixed order)   */
-  int64_t spmm_items;      /* work items of the forward aggregation           */
+  int32_t spmm_segment;    /* runs longer than this are split (fixed order); at
+                              least twice this in sliced plans                */
+  int64_t spmm_items;      /* work items of the forward aggregation (here and
+                              below: of the sliced plan where there is one)   */
   int64_t spmm_split_slots;/* partial-sum slots of split rows (forward)       */
   int64_t spmmt_items;     /* work items of the transposed aggregation        */
   int64_t spmmt_split_slots;

@@ -293,7 +293,7 @@ __global__ __launch_bounds__(256) void agg_kernel(AggParams p) {
 
 // ------------------------------------------------------ L2-resident slices ---
 //
-// Plans with Plan::sliced: rows are cut into slices of kSliceF4 = 16 float4 (256
+// Plans with Plan::sliced set: rows are cut into slices of kSliceF4 = 16 float4 (256
 // bytes) and chunks are small enough that a chunk's rows of one slice fit an XCD's
 // 4 MB L2; workgroup b takes slice b % S, so (dealt round robin) an XCD gathers from
 // one slice only and nearly every load hits its L2.  What bounds it is then the CU's
@@ -779,11 +779,7 @@ int launch_aggregate(const AggArgs &a, hipStream_t s) {
   const int f4 = (a.f + 3) / 4;
   const int C = plan.chunks;
   if (f4 > kMaxAggF4) return set_error(PGCN_EINVAL, "aggregation: feature widths above 63,740 are not supported");
-  // Sliced kernel where the plan is made for it, the rows fit it and both sources and the index
-  // array are within its 32-bit offsets.
-  const bool sliced = plan.sliced && slice_width_ok(a.f) && slice_bytes(a.in_lo ? a.in_split : 0, a.ld_in, f4, 0) >= 0 &&
-                      slice_bytes(a.in_hi ? plan.ncols - a.in_split : 0, a.ld_in, f4, 0) >= 0 &&
-                      plan.nnz < (int64_t)kSliceNowhere / 4 - 64;
+  const bool sliced = plan.sliced != SLICE_NONE;
   ColLaunch cl[256];
   const int ncl = sliced ? slice_launches(f4, cl, 256) : col_launches(f4, cl, 128, plan.nnz >= (int64_t)1 << 20);
   if (ncl < 0) return set_error(PGCN_EINVAL, "aggregation: too many column launches");

@@ -21,37 +21,43 @@ int check_part(const pgcn_partition *p, const char *fn) {
 bool aligned16(const void *q) { return ((uintptr_t)q & 15u) == 0; }
 
 int64_t ld4(int64_t f) { return (f + 3) / 4 * 4; }
-// Row stride of a workspace matrix that an aggregation gathers from: up to 64 floats, a
-// multiple of 8.  A 41-float row then spans 192 bytes, three whole 64-byte lines, where
-// a 44-float stride spreads rows over 3.5 lines on average (measured: the Reddit-like
-// 41-wide aggregation 7% faster).  Wider: an odd number of 128-byte lines, so that the
-// 256-byte slices that an XCD gathers fall on every channel of its L2 (measured: half a
-// Reddit-like transposed aggregation of 256-wide rows, stride 256 -> 288: 575 -> 538 us;
-// R-MAT 1323 -> 1199 us; uniform, 512 -> 544: 1588 -> 1445 us).
-int64_t ldw(int64_t f) { return f <= kNarrowRow ? (f + 7) / 8 * 8 : ((f + 31) / 32 | 1) * 32; }
+// Row stride of a workspace matrix that the aggregation (transposed or not) of rows of f floats
+// gathers from.  For the plain kernel a multiple of 8 floats: a 41-float row then spans 192
+// bytes, three whole 64-byte lines, where a 44-float stride spreads rows over 3.5 lines on
+// average (measured: the Reddit-like 41-wide aggregation 7% faster).  For the sliced one an
+// odd number of 128-byte lines, so that the 256-byte slices that an XCD gathers fall on
+// every channel of its L2 (measured: half a Reddit-like transposed aggregation of 256-wide
+// rows, stride 256 -> 288: 575 -> 538 us; R-MAT 1323 -> 1199 us); elsewhere the longer rows
+// only cost their writes (backward of 32,000 rows without edges, 128 -> 600 in bf16: 89 us at
+// a stride of 128, 98 at 160).
+int64_t ldw(const pgcn_partition *p, bool transposed, int64_t f) {
+  const Plan &sl = transposed ? p->plan_ts : p->plan_s;
+  const int64_t lines = ((f + 31) / 32 | 1) * 32;
+  return slice_width_ok(sl, f) && (p->n_inner + (transposed ? 0 : p->n_bd)) * lines * 4 >= sl.slice_min_bytes
+             ? lines : (f + 7) / 8 * 8;
+}
 
-// Stride of a forward workspace matrix of all n_inner + n_bd rows that is gathered from:
-// ldw's, but a multiple of 8 where the matrix so fits pgcn_layer_fwd_noalloc's scratch
-// array (the layers that fit it have to keep fitting).
-int64_t ld_rows(const pgcn_partition *p, int32_t f) {
+// Stride of a workspace matrix of all n_inner + n_bd rows: ldw's, but a multiple of 8 where the
+// matrix so fits pgcn_layer_fwd_noalloc's scratch array (the layers that fit it have to keep
+// fitting).
+int64_t ld_rows(const pgcn_partition *p, bool transposed, int32_t f) {
   const int64_t tight = ((int64_t)f + 7) / 8 * 8;
-  return (p->n_inner + p->n_bd) * tight * (int64_t)sizeof(float) <= (int64_t)PGCN_NOALLOC_SCRATCH_BYTES ? tight : ldw(f);
+  return (p->n_inner + p->n_bd) * tight * (int64_t)sizeof(float) <= (int64_t)PGCN_NOALLOC_SCRATCH_BYTES
+             ? tight : ldw(p, transposed, f);
 }
 
 // Whether a bf16 forward without an fp32 A aggregates over one chunk straight into the bf16
-// copy, with no running sum: only a plain plan does, which a sliced one keeps as its narrow plan.
-bool one_pass(const pgcn_partition *p, const Plan &pl) {
-  return (pl.sliced ? std::max(pl.plain_chunks, p->plan_n.chunks) : pl.chunks) <= 1 && pl.hub.rows == 0;
-}
+// copy, with no running sum.
+bool one_pass(const Plan &pl) { return pl.chunks <= 1 && pl.hub.rows == 0; }
 bool overlap(const void *a, size_t na, const void *b, size_t nb) {
   const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
   return a && b && x < y + nb && y < x + na;
 }
 // A forward aggregation's plan and where its fp32 sums go.  With an fp32 A they go there.
 // Without (bf16 path), a running sum over chunks takes `acc` (in the workspace); where the
-// plain plan would need none, the sliced one keeps it in H_out, which the update overwrites
-// (products-like 128 -> 128: 1187 -> 1123 us), if a row of H_out holds one of A and H_out
-// overlaps no input; else the plain plan takes the sliced one's place.
+// plain plan would need none, a sliced one of several chunks keeps it in H_out, which the
+// update overwrites (products-like 128 -> 128: 1187 -> 1123 us), if a row of H_out holds one
+// of A and H_out overlaps no input; else the plain plan takes the sliced one's place.
 struct FwdSums {
   const Plan *plan;
   float *lo;
@@ -59,28 +65,26 @@ struct FwdSums {
   bool scratch;
 };
 FwdSums fwd_sums(const pgcn_partition *p, int32_t f_in, int32_t f_out, int32_t gemm_dtype, int64_t ld_in, int64_t ld_out,
-                 const float *in, const float *in_bd, const uint16_t *in16, float *A, const uint16_t *A16, float *H_out,
-                 float *acc) {
-  const Plan &pl = agg_plan(p, false, f_in);
+                 const float *in, const float *in_bd, const uint16_t *in16, const float *agg_lo, const float *agg_hi,
+                 int64_t ld_agg, float *A, const uint16_t *A16, float *H_out, float *acc) {
+  const Plan &plain = plain_plan(p, false, f_in), &pl = agg_plan(p, false, f_in, agg_lo, agg_hi, ld_agg);
   if (A) return FwdSums{&pl, A, ld_in, false};
-  if (!one_pass(p, pl)) return FwdSums{&pl, acc, ld4(f_in), true};
-  if (!pl.sliced) return FwdSums{&pl, nullptr, ld_in, false};
+  if (!one_pass(plain)) return FwdSums{&pl, acc, ld4(f_in), true};
+  if (one_pass(pl)) return FwdSums{&pl, nullptr, ld_in, false};
   const size_t n = (size_t)p->n_inner, h = n * (size_t)ld_out * 4, x = n * (size_t)ld_in * 4;
   if (gemm_dtype == PGCN_BF16 && f_out >= ld4(f_in) && aligned16(H_out) && !overlap(H_out, h, in, x) &&
       !overlap(H_out, h, in_bd, (size_t)p->n_bd * (size_t)ld_in * 4) && !overlap(H_out, h, in16, x / 2) &&
       !overlap(H_out, h, A16, x / 2))
     return FwdSums{&pl, H_out, ld_out, true};
-  return FwdSums{&p->plan_n, nullptr, ld_in, false};
+  return FwdSums{&plain, nullptr, ld_in, false};
 }
-// forward: split-row partials and block sums (of either plan that fwd_sums may pick)
+// forward: split-row partials and block sums
 size_t fwd_part_bytes(const pgcn_partition *p, int32_t f_in) {
-  const Plan &pl = agg_plan(p, false, f_in);
-  const size_t b = aggregate_workspace(pl, f_in);
-  return align_up(pl.sliced && one_pass(p, pl) ? std::max(b, aggregate_workspace(p->plan_n, f_in)) : b, 256);
+  return align_up(aggregate_workspace(plain_plan(p, false, f_in), f_in), 256);
 }
 // ... plus an fp32 running sum over the column chunks when the caller keeps no fp32 A (bf16 path)
 size_t fwd_acc_bytes(const pgcn_partition *p, int32_t f_in, int32_t gemm_dtype) {
-  if (one_pass(p, agg_plan(p, false, f_in)) || gemm_dtype != PGCN_BF16) return 0;
+  if (one_pass(plain_plan(p, false, f_in)) || gemm_dtype != PGCN_BF16) return 0;
   return align_up((size_t)p->n_inner * (size_t)ld4(f_in) * sizeof(float), 256);
 }
 // forward workspace: [aggregation partials | running sum | packed weights]
@@ -92,7 +96,7 @@ size_t fwd_sym_off(const pgcn_partition *p, int32_t f_in, int32_t f_out, int32_t
   return fwd_agg_bytes(p, f_in, gemm_dtype) + gemm_nk_workspace(f_out, f_in, gemm_dtype);
 }
 size_t fwd_ws(const pgcn_partition *p, int32_t f_in, int32_t f_out, int32_t gemm_dtype) {
-  const size_t sym = p->symmetric ? align_up((size_t)(p->n_inner + p->n_bd) * (size_t)ld_rows(p, f_in) * sizeof(float), 256)
+  const size_t sym = p->symmetric ? align_up((size_t)(p->n_inner + p->n_bd) * (size_t)ld_rows(p, false, f_in) * sizeof(float), 256)
                                   : 0;
   return fwd_sym_off(p, f_in, f_out, gemm_dtype) + sym;
 }
@@ -104,8 +108,8 @@ size_t bwd_region0(const pgcn_partition *p, int32_t f_in, int32_t f_out, bool in
   size_t g = gemm_workspace(Gemm::TN_MASK_SPLITK, f_in, f_out, (int32_t)p->n_inner);
   size_t d = 0;
   if (input_grad)
-    d = align_up((size_t)p->n_inner * (size_t)ldw(f_in) * sizeof(float), 256) +
-        align_up(aggregate_workspace(agg_plan(p, true, f_in), f_in), 256);
+    d = align_up((size_t)p->n_inner * (size_t)ldw(p, true, f_in) * sizeof(float), 256) +
+        align_up(aggregate_workspace(plain_plan(p, true, f_in), f_in), 256);
   return align_up(g > d ? g : d, 256);
 }
 // bf16 path with a feature gradient: the masked operand in bf16, written by the
@@ -130,24 +134,24 @@ uint16_t *m16_ptr(const pgcn_partition *p, void *ws, int32_t f_in, int32_t f_out
 // f_out wide) | region R | packed weights]; region R first holds D = diag(1/d)
 // M and the transposed aggregation's partials, then (both consumed) the
 // split-K partials of the weight gradient.
-size_t y_bytes(const pgcn_partition *p, int32_t f_out) {
-  return align_up((size_t)(p->n_inner + p->n_bd) * (size_t)ld_rows(p, f_out) * sizeof(float), 256);
+size_t y_bytes(const pgcn_partition *p, bool transposed, int32_t f_out) {
+  return align_up((size_t)(p->n_inner + p->n_bd) * (size_t)ld_rows(p, transposed, f_out) * sizeof(float), 256);
 }
-size_t fwd_tf_agg_off(const pgcn_partition *p, int32_t f_out) { return y_bytes(p, f_out); }
+size_t fwd_tf_agg_off(const pgcn_partition *p, int32_t f_out) { return y_bytes(p, false, f_out); }
 size_t fwd_tf_gemm_off(const pgcn_partition *p, int32_t f_out) {
-  return y_bytes(p, f_out) + align_up(aggregate_workspace(agg_plan(p, false, f_out), f_out), 256);
+  return y_bytes(p, false, f_out) + align_up(aggregate_workspace(plain_plan(p, false, f_out), f_out), 256);
 }
 size_t fwd_ws_tf(const pgcn_partition *p, int32_t f_in, int32_t f_out, int32_t dt) {
   return fwd_tf_gemm_off(p, f_out) + gemm_nk_workspace(f_out, f_in, dt);
 }
 size_t bwd_tf_region(const pgcn_partition *p, int32_t f_in, int32_t f_out) {
   const size_t g = gemm_workspace(Gemm::TN_MASK_SPLITK, f_in, f_out, (int32_t)(p->n_inner + p->n_bd));
-  const size_t d = align_up((size_t)p->n_inner * (size_t)ld_rows(p, f_out) * sizeof(float), 256) +
-                   align_up(aggregate_workspace(agg_plan(p, true, f_out), f_out), 256);
+  const size_t d = align_up((size_t)p->n_inner * (size_t)ld_rows(p, true, f_out) * sizeof(float), 256) +
+                   align_up(aggregate_workspace(plain_plan(p, true, f_out), f_out), 256);
   return align_up(g > d ? g : d, 256);
 }
 size_t bwd_ws_tf(const pgcn_partition *p, int32_t f_in, int32_t f_out, bool input_grad, int32_t dt) {
-  return y_bytes(p, f_out) + bwd_tf_region(p, f_in, f_out) + (input_grad ? gemm_nk_workspace(f_in, f_out, dt) : 0);
+  return y_bytes(p, true, f_out) + bwd_tf_region(p, f_in, f_out) + (input_grad ? gemm_nk_workspace(f_in, f_out, dt) : 0);
 }
 
 }  // namespace
@@ -211,7 +215,7 @@ int layer_fwd_transform(const pgcn_partition *p, const pgcn_fwd_args *a, hipStre
   const size_t need = fwd_ws_tf(p, a->f_in, a->f_out, a->gemm_dtype);
   if (!a->workspace || a->workspace_bytes < need) return set_error(PGCN_EWORKSPACE, "pgcn_layer_fwd: workspace too small");
   if (p->n_inner == 0) return PGCN_OK;
-  const int64_t ldy = ld_rows(p, a->f_out);
+  const int64_t ldy = ld_rows(p, false, a->f_out);
   float *Y = (float *)a->workspace;
   const bool bd = p->n_bd > 0 && a->H_bd != nullptr;
   GemmArgs m{};
@@ -237,11 +241,11 @@ int layer_fwd_transform(const pgcn_partition *p, const pgcn_fwd_args *a, hipStre
   int rc = launch_gemm_nk(p->d_col_scale ? Gemm::NN_SRC32_ROWSCALE : Gemm::NN_SRC32_PLAIN, m, s);
   if (rc) return rc;
   AggArgs g{};
-  g.plan = &agg_plan(p, false, a->f_out);
   g.col = p->d_col;
   g.in_split = p->n_inner;
   g.in_lo = Y;
   g.in_hi = bd ? Y + p->n_inner * ldy : nullptr;
+  g.plan = &agg_plan(p, false, a->f_out, g.in_lo, g.in_hi, ldy);
   g.out_split = p->n_inner;
   g.out_lo = a->H_out;
   g.scale = p->d_row_scale;
@@ -282,16 +286,16 @@ int layer_bwd_transform(const pgcn_partition *p, const pgcn_bwd_args *a, hipStre
     z.workspace_bytes = a->workspace_bytes;
     return launch_gemm(Gemm::TN_MASK_SPLITK, z, s);
   }
-  const int64_t ldt = ld_rows(p, a->f_out);
+  const int64_t ldt = ld_rows(p, true, a->f_out);
   float *T = (float *)a->workspace;
-  char *R = (char *)a->workspace + y_bytes(p, a->f_out);
+  char *R = (char *)a->workspace + y_bytes(p, true, a->f_out);
   float *D = (float *)R;
   float *partials = (float *)(R + align_up((size_t)p->n_inner * ldt * sizeof(float), 256));
   int rc = launch_mask_scale(a->J_out, a->ld_out, a->relu ? a->H_out : nullptr, a->ld_out, p->d_row_scale, p->n_inner,
                              a->f_out, D, ldt, s);
   if (rc) return rc;
   AggArgs t{};
-  t.plan = &agg_plan(p, true, a->f_out);
+  t.plan = &agg_plan(p, true, a->f_out, D, nullptr, ldt);
   t.col = p->d_col_t;
   t.in_split = p->n_inner;
   t.in_lo = D;
@@ -410,7 +414,7 @@ extern "C" int pgcn_layer_fwd(const pgcn_partition *p, const pgcn_fwd_args *a, h
   const float *in_lo = a->H_in, *in_hi = p->n_bd > 0 ? a->H_bd : nullptr;
   int64_t ld_agg = a->ld_in;
   if (p->d_col_scale) {              // symmetric: the gathered rows scaled by d̃_u^{-1/2} first
-    const int64_t lds = ld_rows(p, a->f_in);
+    const int64_t lds = ld_rows(p, false, a->f_in);
     float *Hs = (float *)((char *)a->workspace + fwd_sym_off(p, a->f_in, a->f_out, a->gemm_dtype));
     rc = launch_mask_scale(a->H_in, a->ld_in, nullptr, 0, p->d_col_scale, p->n_inner, a->f_in, Hs, lds, s);
     if (!rc && in_hi)
@@ -422,8 +426,9 @@ extern "C" int pgcn_layer_fwd(const pgcn_partition *p, const pgcn_fwd_args *a, h
     ld_agg = lds;
   }
   AggArgs g{};
-  const FwdSums sums = fwd_sums(p, a->f_in, a->f_out, a->gemm_dtype, a->ld_in, a->ld_out, a->H_in, a->H_bd, nullptr,
-                                a->A, a->A_bf16, a->H_out, (float *)((char *)a->workspace + fwd_part_bytes(p, a->f_in)));
+  const FwdSums sums = fwd_sums(p, a->f_in, a->f_out, a->gemm_dtype, a->ld_in, a->ld_out, a->H_in, a->H_bd, nullptr, in_lo,
+                                in_hi, ld_agg, a->A, a->A_bf16, a->H_out,
+                                (float *)((char *)a->workspace + fwd_part_bytes(p, a->f_in)));
   g.plan = sums.plan;
   g.col = p->d_col;
   g.in_split = p->n_inner;
@@ -526,7 +531,7 @@ extern "C" int pgcn_layer_bwd(const pgcn_partition *p, const pgcn_bwd_args *a, h
   if (!input_grad || p->n_inner == 0) return PGCN_OK;
 
   // D = diag(1/d) ((J ∘ 1[H > 0]) W^T), then J_full = (P_i^T without the scale) D
-  const int64_t ld_d = ldw(a->f_in);
+  const int64_t ld_d = ldw(p, true, a->f_in);
   float *D = (float *)a->workspace;
   float *partials = (float *)((char *)a->workspace + align_up((size_t)p->n_inner * ld_d * sizeof(float), 256));
   GemmArgs d{};
@@ -555,7 +560,7 @@ extern "C" int pgcn_layer_bwd(const pgcn_partition *p, const pgcn_bwd_args *a, h
   if (rc) return rc;
 
   AggArgs t{};
-  t.plan = &agg_plan(p, true, a->f_in);
+  t.plan = &agg_plan(p, true, a->f_in, D, nullptr, ld_d);
   t.col = p->d_col_t;
   t.in_split = p->n_inner;
   t.in_lo = D;
@@ -596,7 +601,7 @@ int sage_fwd_transform(const pgcn_partition *p, const pgcn_sage_fwd_args *a, hip
   if (!a->workspace || a->workspace_bytes < need)
     return set_error(PGCN_EWORKSPACE, "pgcn_sage_layer_fwd: workspace too small");
   if (p->n_inner == 0) return PGCN_OK;
-  const int64_t ldy = ld_rows(p, a->f_out);
+  const int64_t ldy = ld_rows(p, false, a->f_out);
   float *Y = (float *)a->workspace;
   const bool bd = p->n_bd > 0 && a->X_bd != nullptr;
   GemmArgs m{};
@@ -620,11 +625,11 @@ int sage_fwd_transform(const pgcn_partition *p, const pgcn_sage_fwd_args *a, hip
   int rc = launch_gemm_nk(Gemm::NN_SRC32_PLAIN, m, s);
   if (rc) return rc;
   AggArgs g{};
-  g.plan = &agg_plan(p, false, a->f_out);
   g.col = p->d_col;
   g.in_split = p->n_inner;
   g.in_lo = Y;
   g.in_hi = bd ? Y + p->n_inner * ldy : nullptr;
+  g.plan = &agg_plan(p, false, a->f_out, g.in_lo, g.in_hi, ldy);
   g.out_split = p->n_inner;
   g.out_lo = a->H_out;
   g.scale = p->d_inv_deg;
@@ -692,9 +697,9 @@ int sage_bwd_transform(const pgcn_partition *p, const pgcn_sage_bwd_args *a, hip
     }
     return PGCN_OK;
   }
-  const int64_t ldt = ld_rows(p, a->f_out);
+  const int64_t ldt = ld_rows(p, true, a->f_out);
   float *T = (float *)a->workspace;
-  char *R = (char *)a->workspace + y_bytes(p, a->f_out);
+  char *R = (char *)a->workspace + y_bytes(p, true, a->f_out);
   const size_t region = bwd_tf_region(p, a->f_in, a->f_out);
   float *D = (float *)R;
   float *partials = (float *)(R + align_up((size_t)p->n_inner * ldt * sizeof(float), 256));
@@ -702,7 +707,7 @@ int sage_bwd_transform(const pgcn_partition *p, const pgcn_sage_bwd_args *a, hip
                              a->f_out, D, ldt, s);
   if (rc) return rc;
   AggArgs t{};
-  t.plan = &agg_plan(p, true, a->f_out);
+  t.plan = &agg_plan(p, true, a->f_out, D, nullptr, ldt);
   t.col = p->d_col_t;
   t.in_split = p->n_inner;
   t.in_lo = D;
@@ -837,14 +842,15 @@ extern "C" int pgcn_sage_layer_fwd(const pgcn_partition *p, const pgcn_sage_fwd_
 
   // z = P_i [X_in ; X_bd] (mean over N(v))
   AggArgs g{};
+  const float *x_bd = p->n_bd > 0 ? a->X_bd : nullptr;
   const FwdSums sums = fwd_sums(p, a->f_in, a->f_out, a->gemm_dtype, a->ld_in, a->ld_out, a->X_in, a->X_bd,
-                                a->X_in_bf16, a->A, a->A_bf16, a->H_out,
+                                a->X_in_bf16, a->X_in, x_bd, a->ld_in, a->A, a->A_bf16, a->H_out,
                                 (float *)((char *)a->workspace + fwd_part_bytes(p, a->f_in)));
   g.plan = sums.plan;
   g.col = p->d_col;
   g.in_split = p->n_inner;
   g.in_lo = a->X_in;
-  g.in_hi = p->n_bd > 0 ? a->X_bd : nullptr;
+  g.in_hi = x_bd;
   g.out_split = p->n_inner;
   g.out_lo = sums.lo;
   g.lo_scratch = sums.scratch ? 1 : 0;
@@ -955,7 +961,7 @@ extern "C" int pgcn_sage_layer_bwd(const pgcn_partition *p, const pgcn_sage_bwd_
 
   // J_in = (J ∘ 1[H > 0]) W_bot^T (the self term), D = diag(1/d) ((J ∘ 1[H > 0]) W_top^T),
   // then J_full = (P_i^T without the scale) D, added to the inner rows
-  const int64_t ld_d = ldw(a->f_in);
+  const int64_t ld_d = ldw(p, true, a->f_in);
   float *D = (float *)a->workspace;
   float *partials = (float *)((char *)a->workspace + align_up((size_t)p->n_inner * ld_d * sizeof(float), 256));
   GemmArgs d{};
@@ -989,7 +995,7 @@ extern "C" int pgcn_sage_layer_bwd(const pgcn_partition *p, const pgcn_sage_bwd_
   if (rc) return rc;
 
   AggArgs t{};
-  t.plan = &agg_plan(p, true, a->f_in);
+  t.plan = &agg_plan(p, true, a->f_in, D, nullptr, ld_d);
   t.col = p->d_col_t;
   t.in_split = p->n_inner;
   t.in_lo = D;

@@ -30,7 +30,7 @@ struct SplitRow {
 };
 
 // Fixed work plan over one CSR matrix (rows of P_i or of P_i^T).  The
-// matrix columns are cut into `chunks` ranges (equal ones unless `sliced`); chunk c's items are
+// matrix columns are cut into `chunks` ranges (equal ones in plain plans); chunk c's items are
 // items[chunk_items[c] .. chunk_items[c+1]): first the segments of split rows
 // (items[.. chunk_whole[c])), then one item per other row's run, longest
 // first.  Split rows own `slots` partial slots in total, contiguous per row in
@@ -56,6 +56,10 @@ struct Hub {
   uint32_t *d_bits = nullptr, *d_init = nullptr;
 };
 
+// Widths of gathered rows for which a sliced plan is taken: none (a plain plan), whole launches of
+// 256 floats, widths that fill the slices, every width above kNarrowRow (PGCN_AGG_SLICED=1).
+enum SliceUse { SLICE_NONE, SLICE_WHOLE, SLICE_FULL, SLICE_ALL };
+
 struct Plan {
   int32_t chunks = 1;
   std::vector<WorkItem> items;
@@ -63,8 +67,9 @@ struct Plan {
   std::vector<int64_t> chunk_items, chunk_whole;
   std::vector<int64_t> chunk_cols;  // chunk c holds columns [chunk_cols[c], chunk_cols[c + 1])
   int64_t ncols = 0, nnz = 0;   // columns of the matrix, entries of the array the items index
-  bool sliced = false;          // cut for the sliced kernel: every chunk reads one source matrix
-  int32_t plain_chunks = 1;     // chunks that a plain plan of these rows would have
+  // a plan cut for the sliced kernel (every chunk reads one source matrix): the widths it is taken for
+  SliceUse sliced = SLICE_NONE;
+  int64_t slice_min_bytes = 0;  // ... and the size of the sources from which on it is
   int64_t slots = 0;            // partial slots of all split rows
   WorkItem *d_items = nullptr;
   SplitRow *d_splits = nullptr;
@@ -92,6 +97,8 @@ struct pgcn_partition {
   // plans for gathered rows of at most kNarrowRow floats, whose chunks hold
   // more rows for the same bytes; chunks == 0: not built (same as plan, plan_t)
   pgcn::Plan plan_n, plan_tn;
+  // plans of the sliced kernel for wider rows; chunks == 0: not built
+  pgcn::Plan plan_s, plan_ts;
   // device copies
   int32_t *d_col = nullptr, *d_col_t = nullptr, *d_send_idx = nullptr, *d_inv_k = nullptr;
   int64_t *d_inv_ptr = nullptr;
@@ -123,24 +130,46 @@ inline int64_t slice_bytes(int64_t rows, int64_t ld, int64_t f4, int64_t c4) {
   return b < (int64_t)kSliceNowhere ? b - 16 * c4 : -1;
 }
 
-// Whether the sliced kernel takes rows of f floats: wider than the narrow plans', and not where
-// the last slice would leave more than a quarter of all lanes idle (17 .. 23 float4: 67-wide
-// rows of a uniform graph took 102 us against 79 in the plain kernel).
-inline bool slice_width_ok(int64_t f) {
+// Whether a sliced plan is taken for rows of f floats.  Where the last slice leaves lanes idle,
+// and in launches of one slice, the plain kernel is the faster one.  Aggregations on MI355X,
+// plain over sliced time of the transposed plan (half a Reddit-like, half a products-like, R-MAT
+// and uniform graph): 96 floats (2 slices, 1/4 idle) 0.94, 0.85, 0.96, 0.81; 128 (2) 1.01, 1.09,
+// 1.18, 1.01; 144 (3, 1/4 idle) 0.85, 0.95, 1.12, 0.83; 192 (3) 0.87, 1.13, 1.28, 0.96; 240 (4)
+// 1.19, 1.28, 1.33, 1.02; 256 (4) 1.22, 1.21, 1.32, 1.01; 300 (5) 1.12, 1.27, 1.30, 1.02; 416 (7)
+// 1.02, 1.14, 1.25, 0.92; 512 (8) 1.18, 1.28, 1.28, 1.02.  So: 2 slices or at least 4, 7 of 8
+// lanes busy, and where an L2 holds little of a chunk (SLICE_WHOLE) multiples of 256 floats.
+inline bool slice_width_ok(const Plan &plan, int64_t f) {
   const int64_t f4 = (f + 3) / 4, slices = (f4 + kSliceF4 - 1) / kSliceF4;
-  return f > kNarrowRow && 3 * slices * kSliceF4 <= 4 * f4;
+  if (f <= kNarrowRow || plan.sliced == SLICE_NONE) return false;
+  if (plan.sliced == SLICE_ALL) return true;
+  if (plan.sliced == SLICE_WHOLE) return f4 % (4 * kSliceF4) == 0;
+  return (slices == 2 || slices >= 4) && 8 * f4 >= 7 * slices * kSliceF4;
 }
 
-// The work plan for an aggregation of P_i (transposed: P_i^T) over rows of f floats.  A sliced
-// plan gives way to the plain one, where that is kept as the narrow plan, for rows that the
-// sliced kernel does not take or whose matrices pass its 32-bit offsets.
-inline const Plan &agg_plan(const pgcn_partition *p, bool transposed, int64_t f) {
-  const Plan &narrow = transposed ? p->plan_tn : p->plan_n, &wide = transposed ? p->plan_t : p->plan;
+// The plain work plan for an aggregation of P_i (transposed: P_i^T) over rows of f floats.
+// Scratch memory is sized by it: a sliced plan never takes more partial slots.
+inline const Plan &plain_plan(const pgcn_partition *p, bool transposed, int64_t f) {
+  const Plan &narrow = transposed ? p->plan_tn : p->plan_n;
   if (f <= kNarrowRow && narrow.chunks > 0) return narrow;
-  if (wide.sliced && wide.plain_chunks == narrow.chunks &&
-      (!slice_width_ok(f) || (p->n_inner > p->n_bd ? p->n_inner : p->n_bd) * (f + 64) * 4 > 0xffff0000ll))
-    return narrow;
-  return wide;
+  return transposed ? p->plan_t : p->plan;
+}
+
+// The plan that runs: the sliced one for its widths, if both sources (of n_inner and n_bd rows; the
+// transposed aggregation has the first alone; null: absent) are within the kernel's 32-bit
+// offsets, and if a slice of a row is two whole 128-byte lines.  Where it straddles a third one,
+// plain over sliced time of the forward plan of half a Reddit-like graph is 0.82 at 104 floats
+// a row, 0.76 at 152 and 0.94 at 264.
+inline const Plan &agg_plan(const pgcn_partition *p, bool transposed, int64_t f, const float *lo, const float *hi,
+                            int64_t ld) {
+  const Plan &sl = transposed ? p->plan_ts : p->plan_s, &plain = plain_plan(p, transposed, f);
+  if (!slice_width_ok(sl, f)) return plain;
+  const int64_t f4 = (f + 3) / 4, n_hi = transposed || !hi ? 0 : p->n_bd;
+  if (slice_bytes(lo ? p->n_inner : 0, ld, f4, 0) < 0 || slice_bytes(n_hi, ld, f4, 0) < 0 ||
+      sl.nnz >= (int64_t)kSliceNowhere / 4 - 64)
+    return plain;
+  if (sl.sliced == SLICE_ALL) return sl;
+  if (ld % 32 != 0 || (((uintptr_t)lo | (uintptr_t)hi) & 127u) != 0) return plain;
+  return (p->n_inner + (transposed ? 0 : p->n_bd)) * ld * 4 >= sl.slice_min_bytes ? sl : plain;
 }
 
 int set_error(int code, const std::string &msg) noexcept;
@@ -191,7 +220,7 @@ inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 // goes to out_lo[r], else out_hi[r - out_split].  When `scale` is non-null
 // each output row is multiplied by scale[r].  Partial slots go to `partials`.
 struct AggArgs {
-  const Plan *plan;
+  const Plan *plan;        // a sliced one only as agg_plan gives it
   const int32_t *col;
   int64_t in_split;
   const float *in_lo, *in_hi;

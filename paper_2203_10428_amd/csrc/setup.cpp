@@ -3,6 +3,7 @@
 // S_{i,j} = B_j ∩ V_i, the inverse send map and the fixed work plans of the
 // aggregation kernels.  Host code; the result is uploaded once.
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
@@ -252,26 +253,31 @@ constexpr int64_t kSliceChunkRows = 11000;
 // Rows of one slice that stay in an L2 beside the indices and outputs that pass through it.
 constexpr int64_t kSliceL2Rows = 12288;
 
-// Column cuts of a sliced plan (kernel agg_slice_kernel), empty where the plain plan is
-// the better one.  Columns [0, split) and [split, ncols) come from two matrices and are
-// cut apart; each side takes chunks of about kSliceChunkRows, while a row keeps >= 32
-// non-zeros per chunk.  Worth it (measured on MI355X) where the slices raise the share
-// of gathers that an L2 serves:
+// Column cuts of a sliced plan (kernel agg_slice_kernel), empty where no width is the better for
+// one.  Columns [0, split) and [split, ncols) come from two matrices and are cut apart; each
+// side takes chunks of about kSliceChunkRows, while a row keeps >= 32 non-zeros per chunk.
+// Sets which widths take the plan (`use`, slice_width_ok) and, in bytes of the sources, from
+// where on (`min_bytes`).  Worth it (measured on MI355X) where the slices raise the share of
+// gathers that an L2 serves:
 //  * not below 2^20 non-zeros or 4,096 columns (whole 1 KB rows fit an L2 there);
-//  * the transposed plans gather from a workspace matrix whose stride spreads a slice
-//    over every L2 channel: always (R-MAT 400,000 rows, 256 wide: 1630 -> 1086 us;
-//    uniform 239,000 rows, 512 wide: 1399 -> 1380 us);
-//  * the forward plans gather from the caller's matrices, where a slice of rows of an even
-//    number of 128-byte lines falls on a few of the channels: only if the kSliceL2Rows
-//    most referenced columns of each chunk hold >= a quarter of its non-zeros (R-MAT 0.57
-//    of them: 1654 -> 1215 us; products-like 0.4: 1029 -> 935 us; uniform, 0.05 of them:
-//    1440 -> 1588 us, so not there).
-// PGCN_AGG_SLICED=0 / 1 (environment) never / always cuts so; a chunk count given by
-// PGCN_AGG_CHUNKS or PGCN_AGG_CHUNKS_T is the plain plans' (with PGCN_AGG_SLICED=1, the
-// total over both sides).
+//  * where the kSliceL2Rows most referenced columns of each chunk hold >= a quarter of its
+//    non-zeros.  Below that only the transposed plans gain, a little and in whole launches:
+//    uniform, 239,000 rows (0.12 of them held), plain over sliced time 1.01 at 256 and 512
+//    floats, 0.90 to 0.99 at 224, 288 and 416; forward 512 floats 1440 -> 1588 us;
+//  * a chunk more than the plain plan's moves each output row twice, for runs that are
+//    shorter by as much: with under 24 non-zeros a run, and sources that the 256 MB last-level
+//    cache serves, the forward is slower sliced.  Plain over sliced time at 128, 256, 384
+//    and 512 floats: R-MAT of 144,000 source rows (runs of 15) 0.74, 0.96, 0.84, 1.05, power
+//    law of 165,000 (15) 0.75, 1.05, 0.96, 1.12; R-MAT of 567,000 (17) 1.28, 1.26, 1.29, 1.19,
+//    products-like of 228,000 (25) 1.11, 1.19, 1.16, 1.18.  Hence 400 MB below 24.
+// PGCN_AGG_SLICED=0 / 1 (environment) never / always cuts so, for every width above kNarrowRow;
+// a chunk count given by PGCN_AGG_CHUNKS or PGCN_AGG_CHUNKS_T is the plain plans' (with
+// PGCN_AGG_SLICED=1, the total over both sides).
 static std::vector<int64_t> choose_slices(const std::vector<int64_t> &rowptr, const std::vector<int32_t> &col,
                                           int64_t nrows, int64_t ncols, int64_t split, bool transposed,
-                                          int32_t plain_chunks) {
+                                          int32_t plain_chunks, SliceUse &use, int64_t &min_bytes) {
+  use = SLICE_NONE;
+  min_bytes = 0;
   const char *env = std::getenv("PGCN_AGG_SLICED");
   const bool forced = env && std::strcmp(env, "1") == 0;
   const int64_t nnz = (int64_t)col.size();
@@ -292,7 +298,10 @@ static std::vector<int64_t> choose_slices(const std::vector<int64_t> &rowptr, co
   for (int64_t c = 0; c < clo; ++c) cuts.push_back(split * c / clo);
   for (int64_t c = 0; c < chi; ++c) cuts.push_back(split + (ncols - split) * c / chi);
   cuts.push_back(ncols);
-  if (forced || transposed) return cuts;
+  if (forced) {
+    use = SLICE_ALL;
+    return cuts;
+  }
   int64_t held = 0;
   for (size_t c = 0; c + 1 < cuts.size(); ++c) {
     std::vector<int64_t> part(refs.begin() + cuts[c], refs.begin() + cuts[c + 1]);
@@ -303,8 +312,14 @@ static std::vector<int64_t> choose_slices(const std::vector<int64_t> &rowptr, co
     held += std::accumulate(part.begin(), part.end(), (int64_t)0);
   }
   // every chunk more than the plain plan's moves each output row twice: the gathers it has to save
-  const int64_t moved = 2 * nrows * std::max<int64_t>(0, (int64_t)cuts.size() - 1 - plain_chunks);
-  return 4 * (held - moved) >= nnz ? cuts : std::vector<int64_t>{};
+  const int64_t chunks = (int64_t)cuts.size() - 1, moved = 2 * nrows * std::max<int64_t>(0, chunks - plain_chunks);
+  if (4 * (held - moved) >= nnz) {
+    use = SLICE_FULL;
+    if (chunks > plain_chunks && nnz < 24 * nrows * chunks) min_bytes = (int64_t)400 << 20;
+  } else if (transposed && chunks <= plain_chunks) {
+    use = SLICE_WHOLE;
+  }
+  return use == SLICE_NONE ? std::vector<int64_t>{} : cuts;
 }
 
 // Work plan of one aggregation over the column chunks `cuts`.  A row whose run inside
@@ -380,25 +395,27 @@ static int upload(T **dptr, const std::vector<T> &h) {
   return PGCN_OK;
 }
 
-// A narrow plan of a matrix takes its wide plan's dense block: the block's sizes, and its
+// A narrow or sliced plan of a matrix takes its wide plan's dense block: the block's sizes, and its
 // device arrays once uploaded (borrowed: free_device frees them through the wide plan).
-static void share_hub(const Plan &wide, Plan &narrow) {
-  narrow.hub.rows = wide.hub.rows;
-  narrow.hub.rows_real = wide.hub.rows_real;
-  narrow.hub.cols = wide.hub.cols;
-  narrow.hub.cols_real = wide.hub.cols_real;
-  narrow.hub.nnz = wide.hub.nnz;
-  narrow.hub.d_row_ids = wide.hub.d_row_ids;
-  narrow.hub.d_col_ids = wide.hub.d_col_ids;
-  narrow.hub.d_bits = wide.hub.d_bits;
-  narrow.hub.d_init = wide.hub.d_init;
-  narrow.d_col_rest = wide.d_col_rest;
+static void share_hub(const Plan &wide, Plan &other) {
+  other.hub.rows = wide.hub.rows;
+  other.hub.rows_real = wide.hub.rows_real;
+  other.hub.cols = wide.hub.cols;
+  other.hub.cols_real = wide.hub.cols_real;
+  other.hub.nnz = wide.hub.nnz;
+  other.hub.d_row_ids = wide.hub.d_row_ids;
+  other.hub.d_col_ids = wide.hub.d_col_ids;
+  other.hub.d_bits = wide.hub.d_bits;
+  other.hub.d_init = wide.hub.d_init;
+  other.d_col_rest = wide.d_col_rest;
+}
+
+static std::array<Plan *, 6> all_plans(pgcn_partition *p) noexcept {
+  return {&p->plan, &p->plan_t, &p->plan_n, &p->plan_tn, &p->plan_s, &p->plan_ts};
 }
 
 static void free_device(pgcn_partition *p) {
-  void *ptrs[] = {p->d_col, p->d_col_t, p->d_send_idx, p->d_inv_k, p->d_inv_ptr, p->d_inv_deg, p->d_sym_scale,
-                  p->plan.d_items, p->plan.d_splits, p->plan_t.d_items, p->plan_t.d_splits,
-                  p->plan_n.d_items, p->plan_n.d_splits, p->plan_tn.d_items, p->plan_tn.d_splits};
+  void *ptrs[] = {p->d_col, p->d_col_t, p->d_send_idx, p->d_inv_k, p->d_inv_ptr, p->d_inv_deg, p->d_sym_scale};
   for (void *q : ptrs)
     if (q) (void)hipFree(q);
   for (Plan *q : {&p->plan, &p->plan_t}) {
@@ -406,7 +423,11 @@ static void free_device(pgcn_partition *p) {
     for (void *x : hp)
       if (x) (void)hipFree(x);
   }
-  for (Plan *q : {&p->plan, &p->plan_t, &p->plan_n, &p->plan_tn}) {   // the narrow plans' are borrowed
+  for (Plan *q : all_plans(p)) {       // the narrow and sliced plans' blocks are borrowed
+    if (q->d_items) (void)hipFree(q->d_items);
+    if (q->d_splits) (void)hipFree(q->d_splits);
+    q->d_items = nullptr;
+    q->d_splits = nullptr;
     q->d_col_rest = nullptr;
     q->hub.d_row_ids = q->hub.d_col_ids = nullptr;
     q->hub.d_bits = q->hub.d_init = nullptr;
@@ -415,8 +436,6 @@ static void free_device(pgcn_partition *p) {
   p->d_inv_ptr = nullptr;
   p->d_inv_deg = p->d_sym_scale = nullptr;
   p->d_row_scale = p->d_col_scale = nullptr;
-  p->plan.d_items = p->plan_t.d_items = p->plan_n.d_items = p->plan_tn.d_items = nullptr;
-  p->plan.d_splits = p->plan_t.d_splits = p->plan_n.d_splits = p->plan_tn.d_splits = nullptr;
 }
 
 // The graph must be undirected: v lists u exactly when u lists v (self loops
@@ -661,37 +680,37 @@ extern "C" int pgcn_partition_setup(const pgcn_csr *csr, const pgcn_boundary_map
     const int32_t cn = choose_chunks(n_in, n_all, nnz, false, narrow, true);
     const int32_t ctn = choose_chunks(n_all, n_in, nnz, true, narrow, true);
     // a matrix may have a dense block on the matrix cores; every plan of it then indexes the
-    // rest, and the narrow plan uses the wide plan's block (the same matrix, the same block).
-    // Wide plan: sliced where that pays, else equal chunks.  The sliced kernel gives a row's
-    // segment to 16 lanes and takes segments twice as long at the same speed; longer still if
-    // the plan would otherwise take more partial slots than the plain one.
+    // rest, and the other plans use the wide plan's block (the same matrix, the same block).
+    // The sliced kernel gives a row's segment to 16 lanes and takes segments twice as long at the
+    // same speed; longer still if the plan would otherwise take more partial slots than the
+    // plain one, whose scratch memory it runs in.  (That ends: rows of up to `segment` times the
+    // plain plan's chunks may be whole in both, and of any longer one the plain plan has a slot
+    // per `segment` non-zeros.)
     auto plans = [p, n_in](const std::vector<int64_t> &rp_all, const std::vector<int32_t> &cl_all, int64_t nrows,
-                           int64_t ncols, bool transposed, int32_t chunks, int32_t chunks_narrow, Plan &plan, Plan &nar) {
+                           int64_t ncols, bool transposed, int32_t chunks, int32_t chunks_narrow, Plan &plan, Plan &nar,
+                           Plan &sl) {
       std::vector<int64_t> rp_rest;
       choose_hub(rp_all, cl_all, nrows, ncols, plan.hub, rp_rest, plan.col_rest);
       const bool hub = plan.hub.rows > 0;
       const std::vector<int64_t> &rp = hub ? rp_rest : rp_all;
       const std::vector<int32_t> &cl = hub ? plan.col_rest : cl_all;
-      const std::vector<int64_t> plain = equal_cuts(ncols, chunks),
-                                 cuts = choose_slices(rp, cl, nrows, ncols, n_in, transposed, chunks);
-      plan.sliced = !cuts.empty();
-      plan.plain_chunks = chunks;
-      int64_t segment = p->segment;
-      if (plan.sliced) {
-        const int64_t most = plan_slots(rp, cl, nrows, plain, segment);
-        segment *= 2;
-        while (plan_slots(rp, cl, nrows, cuts, segment) > most) segment *= 2;
-      }
-      build_plan(rp, cl, nrows, plan.sliced ? cuts : plain, segment, plan);
-      nar.chunks = 0;
-      if (chunks_narrow != chunks || plan.sliced) {
+      build_plan(rp, cl, nrows, equal_cuts(ncols, chunks), p->segment, plan);
+      nar.chunks = sl.chunks = 0;
+      if (chunks_narrow != chunks) {
         build_plan(rp, cl, nrows, equal_cuts(ncols, chunks_narrow), p->segment, nar);
         share_hub(plan, nar);
       }
+      const std::vector<int64_t> cuts =
+          choose_slices(rp, cl, nrows, ncols, n_in, transposed, chunks, sl.sliced, sl.slice_min_bytes);
+      if (cuts.empty()) return;
+      int64_t segment = 2 * (int64_t)p->segment;
+      while (plan_slots(rp, cl, nrows, cuts, segment) > plan.slots) segment *= 2;
+      build_plan(rp, cl, nrows, cuts, segment, sl);
+      share_hub(plan, sl);
     };
     // the two sides share nothing but their inputs: P_i^T's plans on a second thread (products-like
     // set-up 8.8 s in turn, 5.7 s so on the same CPUs)
-    auto side_t = [&] { plans(p->rowptr_t, p->col_t, n_all, n_in, true, ct, ctn, p->plan_t, p->plan_tn); };
+    auto side_t = [&] { plans(p->rowptr_t, p->col_t, n_all, n_in, true, ct, ctn, p->plan_t, p->plan_tn, p->plan_ts); };
     std::future<void> other;
     if (nnz >= (int64_t)1 << 16) {
       try {
@@ -699,7 +718,7 @@ extern "C" int pgcn_partition_setup(const pgcn_csr *csr, const pgcn_boundary_map
       } catch (const std::system_error &) {            // no thread to be had: in turn, below
       }
     }
-    plans(p->rowptr, p->col, n_in, n_all, false, c, cn, p->plan, p->plan_n);
+    plans(p->rowptr, p->col, n_in, n_all, false, c, cn, p->plan, p->plan_n, p->plan_s);
     if (other.valid()) other.get();
     else side_t();
   }
@@ -714,14 +733,10 @@ extern "C" int pgcn_partition_setup(const pgcn_csr *csr, const pgcn_boundary_map
     if (!rc) rc = upload(&p->d_inv_ptr, p->inv_ptr);
     if (!rc) rc = upload(&p->d_inv_deg, p->inv_deg);
     if (!rc && p->symmetric) rc = upload(&p->d_sym_scale, p->sym_scale);
-    if (!rc) rc = upload(&p->plan.d_items, p->plan.items);
-    if (!rc) rc = upload(&p->plan.d_splits, p->plan.splits);
-    if (!rc) rc = upload(&p->plan_t.d_items, p->plan_t.items);
-    if (!rc) rc = upload(&p->plan_t.d_splits, p->plan_t.splits);
-    if (!rc) rc = upload(&p->plan_n.d_items, p->plan_n.items);
-    if (!rc) rc = upload(&p->plan_n.d_splits, p->plan_n.splits);
-    if (!rc) rc = upload(&p->plan_tn.d_items, p->plan_tn.items);
-    if (!rc) rc = upload(&p->plan_tn.d_splits, p->plan_tn.splits);
+    for (Plan *q : all_plans(p)) {
+      if (!rc) rc = upload(&q->d_items, q->items);
+      if (!rc) rc = upload(&q->d_splits, q->splits);
+    }
     for (Plan *q : {&p->plan, &p->plan_t}) {
       if (!rc) rc = upload(&q->d_col_rest, q->col_rest);
       if (!rc) rc = upload(&q->hub.d_row_ids, q->hub.row_ids);
@@ -730,8 +745,10 @@ extern "C" int pgcn_partition_setup(const pgcn_csr *csr, const pgcn_boundary_map
       if (!rc) rc = upload(&q->hub.d_init, q->hub.init);
     }
     if (rc) return rc;
-    if (p->plan_n.chunks > 0) share_hub(p->plan, p->plan_n);
-    if (p->plan_tn.chunks > 0) share_hub(p->plan_t, p->plan_tn);
+    for (Plan *q : {&p->plan_n, &p->plan_s})
+      if (q->chunks > 0) share_hub(p->plan, *q);
+    for (Plan *q : {&p->plan_tn, &p->plan_ts})
+      if (q->chunks > 0) share_hub(p->plan_t, *q);
     p->d_row_scale = p->symmetric ? p->d_sym_scale : p->d_inv_deg;
     p->d_col_scale = p->symmetric ? p->d_sym_scale : nullptr;
   }
@@ -753,12 +770,13 @@ extern "C" int pgcn_partition_info(const pgcn_partition *p, pgcn_info *o) try {
   o->self = p->self;
   o->host_only = p->host_only;
   o->spmm_segment = p->segment;
-  o->spmm_items = (int64_t)p->plan.items.size();
-  o->spmm_split_slots = p->plan.slots;
-  o->spmmt_items = (int64_t)p->plan_t.items.size();
-  o->spmmt_split_slots = p->plan_t.slots;
-  o->spmm_chunks = p->plan.chunks;
-  o->spmmt_chunks = p->plan_t.chunks;
+  const Plan &wide = p->plan_s.chunks ? p->plan_s : p->plan, &wide_t = p->plan_ts.chunks ? p->plan_ts : p->plan_t;
+  o->spmm_items = (int64_t)wide.items.size();
+  o->spmm_split_slots = wide.slots;
+  o->spmmt_items = (int64_t)wide_t.items.size();
+  o->spmmt_split_slots = wide_t.slots;
+  o->spmm_chunks = wide.chunks;
+  o->spmmt_chunks = wide_t.chunks;
   o->spmm_chunks_narrow = p->plan_n.chunks ? p->plan_n.chunks : p->plan.chunks;
   o->spmmt_chunks_narrow = p->plan_tn.chunks ? p->plan_tn.chunks : p->plan_t.chunks;
   o->spmm_hub_rows = p->plan.hub.rows_real;

@@ -1,5 +1,6 @@
-"""The sliced aggregation kernel (PGCN_AGG_SLICED=1 takes it on any graph; large
-partitions select it by themselves) against fp64 sums and through whole layers.
+"""The sliced aggregation kernel (PGCN_AGG_SLICED=1 takes it on any graph and for every
+row of more than 64 floats, as tests/test_plan_rules_cpu.py pins; large partitions
+select it by themselves) against fp64 sums and through whole layers.
 
 Element-wise bound of a row sum of d terms added in fp32 in any order, over C
 chunks and scaled by one rounded factor: (d + C + 2) 2^-24 times the sum of the
@@ -113,6 +114,60 @@ def test_sources_may_be_views_of_wider_matrices(f):
     del keep, keep_bd
 
 
+@pytest.mark.parametrize("ld", [800_000, 1_600_000])
+def test_sources_of_some_gigabytes(ld):
+    """Row strides that put the last row beyond 2 GiB (offsets of 32 bits, above the sign bit), and beyond 4
+    GiB, which the plain kernel takes."""
+    f, (n_g, rowptr, col, owner, nparts) = 100, graph("hubs")
+    part = setup(SLICED, n_g, rowptr, col, owner, nparts)
+    P = propagation_matrix(build_partition(n_g, rowptr, col, owner, 0, nparts), "mean")
+    info = B.pgcn_partition_info(part)
+    n, b = info["n_inner"], info["n_bd"]
+    assert (1 << 31) < 4 * (n - 1) * ld and (4 * n * ld < 1 << 32) == (ld == 800_000)
+    X = np.random.default_rng(f).standard_normal((n + b, f)).astype(np.float32)
+
+    def mat(x):
+        t = torch.empty((x.shape[0], ld), device="cuda")
+        t[:, :f + 60] = float("nan")
+        t[:, :f] = torch.from_numpy(x).cuda()
+        return t
+
+    nb = B.pgcn_workspace_size(part, f, 8, B.PGCN_F32)
+    A = torch.empty((n, ld), device="cuda")
+    B.pgcn_layer_fwd(part, f_in=f, f_out=8, gemm_dtype=B.PGCN_F32, relu=False, ld_in=ld, ld_out=8, H_in=mat(X[:n]),
+                     H_bd=mat(X[n:]), W=torch.ones((f, 8), device="cuda"), A=A, A_bf16=None, H_out=dev(np.zeros((n, 8))),
+                     workspace=torch.empty(nb, dtype=torch.uint8, device="cuda"), workspace_bytes=nb)
+    Xd, d = X.astype(np.float64), np.diff(P.indptr)[:, None]
+    assert np.all(np.abs(host(A, f) - P @ Xd) <= (d + 8) * U * (P @ np.abs(Xd)))
+
+
+@pytest.mark.parametrize("f,shift,same", [(72, 0, True), (100, 0, True), (144, 0, True), (192, 0, True), (128, 0, False),
+                                          (256, 0, False), (256, 8, True), (264, 0, True), (320, 0, False)])
+def test_default_plans_by_width_and_alignment(f, shift, same):
+    """On a graph with a sliced plan, the calls that leave it (widths that do not fill the slices, rows
+    whose slices straddle lines) give the plain plan's results bit for bit; the others' sums are
+    formed in another order and chunks."""
+    n_g, rowptr, col, owner = random_partition_graph(9000, 4500, 3, 150, 31)
+    outs = []
+    for env in ({"PGCN_AGG_SLICED": "0"}, {}):
+        part = setup(env, n_g, rowptr, col, owner, 3)
+        info = B.pgcn_partition_info(part)
+        n, b, ld = info["n_inner"], info["n_bd"], ld_of(f)
+        X = torch.randn((n + b) * ld + 8, generator=torch.Generator("cuda").manual_seed(f), device="cuda")
+        H_in, H_bd = X.data_ptr() + 4 * shift, X.data_ptr() + 4 * (n * ld + shift)
+        nb = B.pgcn_workspace_size(part, f, 8, B.PGCN_F32)
+        A = torch.zeros((n, ld), device="cuda")
+        B.pgcn_layer_fwd(part, f_in=f, f_out=8, gemm_dtype=B.PGCN_F32, relu=False, ld_in=ld, ld_out=8, H_in=H_in,
+                         H_bd=H_bd, W=torch.ones((f, 8), device="cuda"), A=A, A_bf16=None, H_out=dev(np.zeros((n, 8))),
+                         workspace=torch.empty(nb, dtype=torch.uint8, device="cuda"), workspace_bytes=nb)
+        torch.cuda.synchronize()
+        outs.append(A[:, :f])
+    assert info["nnz"] >= 1 << 20 and torch.equal(*outs) == same
+    deg = torch.from_numpy(np.diff(rowptr)[:n] + 1).cuda()[:, None]
+    # two orders of a mean of at most deg normal values of magnitude <= 6
+    assert torch.all((outs[0] - outs[1]).abs() <= 2 * (deg + 8) * U * 6)
+
+
 @pytest.mark.parametrize("f", [257, 300, 380, 440, 600])
 def test_row_sums_with_the_remainder_joined(f):
     """The plain kernel on a matrix of over 2^20 non-zeros: the last full slice of 64 float4 takes
@@ -146,9 +201,20 @@ def test_layers(model, norm, order, dt, f_in, f_out, env):
 @pytest.mark.parametrize("f_in,f_out,in_place", [(72, 64, False), (256, 256, False), (100, 104, False), (130, 132, False),
                                                  (128, 128, True)])
 def test_bf16_without_fp32_aggregate(f_in, f_out, in_place):
+    sizes, info = check_bf16_without_fp32_aggregate(f_in, f_out, in_place)
+    assert sizes[0] == sizes[1] and info["spmm_chunks"] == 2
+
+
+@pytest.mark.parametrize("f_in,f_out", [(100, 64), (256, 128), (141, 144), (93, 96)])
+def test_bf16_without_fp32_aggregate_partial_slices(f_in, f_out):
+    check_bf16_without_fp32_aggregate(f_in, f_out, False)
+
+
+def check_bf16_without_fp32_aggregate(f_in, f_out, in_place):
     """One plain chunk and no dense block: the plain plan keeps no running sum, and a sliced one
-    keeps it in H_out where a row of it holds one of A and H_out is no input (72 -> 64 and in
-    place: the plain plan, bit for bit).  The workspace is the plain plan's in every case."""
+    keeps it in H_out where a row of it holds one of A and H_out is no input (72 -> 64, 100 ->
+    64, 256 -> 128 and in place: the plain plan, bit for bit).  The workspace that the plain plan
+    asks for is enough in every case."""
     n_g, rowptr, col, owner, nparts = graph("hubs")
     P = propagation_matrix(build_partition(n_g, rowptr, col, owner, 0, nparts), "mean")
     outs, sizes = [], []
@@ -159,7 +225,8 @@ def test_bf16_without_fp32_aggregate(f_in, f_out, in_place):
         rng = np.random.default_rng(f_in)
         X = rng.standard_normal((n + b, f_in)).astype(np.float32)
         W = torch.from_numpy(rng.standard_normal((f_in, f_out)).astype(np.float32)).cuda()
-        nb = B.pgcn_workspace_size(part, f_in, f_out, B.PGCN_BF16)
+        sizes.append(B.pgcn_workspace_size(part, f_in, f_out, B.PGCN_BF16))
+        nb = sizes[0]
         A16 = torch.zeros((n, ld_of(f_in)), dtype=torch.bfloat16, device="cuda")
         H_in = dev(X[:n])
         H = H_in if in_place else torch.full((n, ld_of(f_out)), 5.0, device="cuda")
@@ -167,11 +234,9 @@ def test_bf16_without_fp32_aggregate(f_in, f_out, in_place):
                          ld_out=ld_of(f_out), H_in=H_in, H_bd=dev(X[n:]), W=W, A=None, A_bf16=A16, H_out=H,
                          workspace=torch.empty(nb, dtype=torch.uint8, device="cuda"), workspace_bytes=nb)
         outs.append((A16, H))
-        sizes.append(nb)
-    assert sizes[0] == sizes[1] and info["spmm_chunks"] == 2
     if in_place or f_out < (f_in + 3) // 4 * 4:
         assert torch.equal(outs[0][0], outs[1][0]) and torch.equal(outs[0][1], outs[1][1])
-        return
+        return sizes, info
     assert torch.equal(outs[1][1][:, f_out:], outs[0][1][:, f_out:])        # H_out's padding is left alone
     Xd, d = X.astype(np.float64), np.diff(P.indptr)[:, None]
     exact, mag = P @ Xd, P @ np.abs(Xd)
@@ -181,3 +246,4 @@ def test_bf16_without_fp32_aggregate(f_in, f_out, in_place):
         Wb = W.bfloat16().double().cpu().numpy()
         Zb = np.maximum(got @ Wb, 0.0)
         assert np.all(np.abs(host(H, f_out) - Zb) <= (f_in + 2) * U * (np.abs(got) @ np.abs(Wb)))
+    return sizes, info

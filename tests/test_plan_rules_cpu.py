@@ -1,12 +1,16 @@
-"""Host rules of the kernel launches (no GPU): the range of memory that the sliced
-aggregation's buffer resource covers, the node splits of the weight gradient and the
-side from which sent rows are packed."""
+"""Host rules of the kernel launches (no GPU): which matrices get sliced aggregation
+plans and which calls take them, the range of memory that the sliced kernel's buffer
+resource covers, the node splits of the weight gradient and the side from which sent
+rows are packed."""
 import ctypes as C
 import os
 import subprocess
 
+import numpy as np
 import pytest
 
+from gpu_helpers import random_partition_graph
+from paper_2203_10428_amd import binding as B
 from paper_2203_10428_amd import build
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -21,6 +25,8 @@ def probe(tmp_path_factory):
     lib.probe_slice_bytes.restype = _i64
     lib.probe_slice_bytes.argtypes = [_i64] * 4
     lib.probe_pack_by_row.argtypes = [_i64] * 5
+    lib.probe_plan.argtypes = [C.c_void_p, C.c_int, C.c_int, C.c_void_p]
+    lib.probe_taken.argtypes = [C.c_void_p, C.c_int, _i64, _i64, _i64, _i64]
     return lib
 
 
@@ -62,3 +68,102 @@ def test_rows_packed_by_inner_row(probe, f, ld, dst, most):
     rows = 1000
     by_row = [r for r in (1, 2, 8, 40) if probe.probe_pack_by_row(r * rows, rows, (f + 3) // 4, ld, dst)]
     assert by_row == [r for r in (2, 8, 40) if r <= most]
+
+
+# ------------------------------------------------------------- sliced plans ---
+
+PLAIN, NARROW, SLICED = range(3)
+NONE, WHOLE, FULL, ALL = range(4)
+AT = 1 << 20                                             # an address of whole lines
+
+
+@pytest.fixture
+def clean(monkeypatch):
+    for k in ("PGCN_AGG_CHUNKS", "PGCN_AGG_CHUNKS_T", "PGCN_AGG_CHUNKS_NARROW", "PGCN_AGG_SLICED", "PGCN_SEGMENT"):
+        monkeypatch.delenv(k, raising=False)
+    return monkeypatch
+
+
+def plan(probe, part, transposed, which):
+    out = (_i64 * 256)()
+    n = probe.probe_plan(part.handle, transposed, which, out)
+    return dict(zip(("chunks", "slots", "use", "min_bytes"), out[:4]), cuts=list(out[4:n]))
+
+
+def skewed_graph(n_inner, n_pool, m, seed, columns):
+    """`m` edges of which 0.7 have an end among the first `columns` nodes of either kind."""
+    rng = np.random.default_rng(seed)
+    n = n_inner + n_pool
+    u = rng.integers(0, n_inner, m)
+    v = np.where(rng.random(m) < 0.7, rng.integers(0, columns, m) + n_inner * (rng.random(m) < 0.3), rng.integers(0, n, m))
+    u, v = u[u != v], v[u != v]
+    key = np.unique(np.concatenate([u * n + v, v * n + u]))
+    rowptr = np.searchsorted(key, np.arange(n + 1) * n).astype(np.int64)
+    return n, rowptr, (key % n).astype(np.int32), (np.arange(n) >= n_inner).astype(np.int32)
+
+
+def uniform_graph(n_inner, n_pool, deg):
+    return random_partition_graph(n_inner, n_pool, 2, deg, 3)
+
+
+@pytest.mark.parametrize("graph,forward,transposed", [
+    # below 2^20 non-zeros: plain plans
+    (lambda: uniform_graph(8000, 4500, 100), NONE, NONE),
+    # dense enough that whole chunks stay in an L2
+    (lambda: uniform_graph(9000, 4500, 140), FULL, FULL),
+    # sparse: an L2 holds a tenth of the gathers of a uniform graph, most of a skewed one's
+    (lambda: uniform_graph(120000, 60000, 11), NONE, WHOLE),
+    (lambda: skewed_graph(60000, 30000, 700000, 5, 2000), FULL, FULL)])
+def test_default_choice_of_sliced_plans(probe, clean, graph, forward, transposed):
+    n, rowptr, col, owner = graph()
+    part = B.pgcn_partition_setup(n, rowptr, col, owner, 2, 0, host_only=True)
+    info = B.pgcn_partition_info(part)
+    n_in, n_bd, nnz = info["n_inner"], info["n_bd"], info["nnz"]
+    assert (nnz >= 1 << 20) == (transposed != NONE) and max(n_in, n_bd) > 4096
+    for t, use, nrows, sides in ((0, forward, n_in, (n_in, n_bd)), (1, transposed, n_in + n_bd, (n_in,))):
+        plain, sl = plan(probe, part, t, PLAIN), plan(probe, part, t, SLICED)
+        assert plain["use"] == NONE and sl["use"] == use
+        assert info["spmmt_chunks" if t else "spmm_chunks"] == (sl if use else plain)["chunks"]
+        if use == NONE:
+            assert sl["chunks"] == 0
+            continue
+        assert sl["slots"] <= plain["slots"]             # the scratch memory is sized by the plain plan
+        cuts = sl["cuts"]
+        assert cuts[0] == 0 and cuts[-1] == sum(sides) and all(s in cuts for s in np.cumsum(sides))
+        for a, b in zip(cuts, cuts[1:]):
+            assert 0 < b - a and (b - a <= 16500 or nnz // nrows < 64)
+        short = len(cuts) - 1 > plain["chunks"] and nnz < 24 * nrows * (len(cuts) - 1)
+        assert sl["min_bytes"] == (400 << 20 if short else 0)
+        for f, full in ((64, 0), (65, 0), (96, 0), (112, 1), (128, 1), (144, 0), (192, 0), (200, 0), (224, 1), (256, 1),
+                        (300, 1), (512, 1), (602, 1)):
+            ld = -(-f // 32) * 32 if not short else 1 << 13
+            takes = bool(full) if use == FULL else f % 256 == 0
+            assert (probe.probe_taken(part.handle, t, f, AT, 0 if t else AT, ld) == SLICED) == takes, (t, f)
+
+
+def test_calls_that_leave_the_sliced_plan(probe, clean):
+    """Sources whose slices straddle lines, sources of 4 GiB and sources that the caches serve run the
+    plain plan, as narrow rows and refused widths do; PGCN_AGG_SLICED=1 keeps all but the 4 GiB ones."""
+    n, rowptr, col, owner = uniform_graph(9000, 4500, 140)
+    part = B.pgcn_partition_setup(n, rowptr, col, owner, 2, 0, host_only=True)
+    took = lambda f, lo, hi, ld, t=0: probe.probe_taken(part.handle, t, f, lo, hi, ld)
+    assert took(256, AT, AT, 256) == took(256, AT, 0, 256) == took(256, AT, 0, 256, 1) == SLICED
+    assert took(256, AT, AT, 260) == took(256, AT + 64, AT, 256) == took(256, AT, AT + 16, 256) == PLAIN
+    limit = 0xfffff000 // 4 // 8999 // 32 * 32           # the second row of 9,000 that passes 32-bit offsets
+    assert took(256, AT, AT, limit - 32) == SLICED and took(256, AT, AT, limit + 32) == PLAIN
+    n, rowptr, col, owner = skewed_graph(60000, 30000, 700000, 5, 2000)
+    part = B.pgcn_partition_setup(n, rowptr, col, owner, 2, 0, host_only=True)
+    info = B.pgcn_partition_info(part)
+    rows = info["n_inner"] + info["n_bd"]
+    least = plan(probe, part, 0, SLICED)["min_bytes"]
+    assert least == 400 << 20
+    ld = -(-(least // 4 // rows) // 32) * 32
+    assert took(256, AT, AT, ld + 32) == SLICED and took(256, AT, AT, ld - 32) == PLAIN
+    clean.setenv("PGCN_AGG_SLICED", "1")
+    part = B.pgcn_partition_setup(n, rowptr, col, owner, 2, 0, host_only=True)
+    for f in (65, 72, 100, 144, 300, 602):
+        assert took(f, AT + 16, AT, f // 4 * 4 + 4) == took(f, AT, 0, f // 4 * 4 + 4, 1) == SLICED
+    assert took(64, AT, AT, 64) != SLICED and took(72, AT, AT, 1 << 15) == PLAIN
+    clean.setenv("PGCN_AGG_SLICED", "0")
+    part = B.pgcn_partition_setup(n, rowptr, col, owner, 2, 0, host_only=True)
+    assert took(256, AT, AT, 1 << 11) == PLAIN and plan(probe, part, 1, SLICED)["chunks"] == 0
