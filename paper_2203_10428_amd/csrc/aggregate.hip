@@ -669,11 +669,14 @@ static int slice_width() {
 }
 
 //
-// With `join` the last full slice takes the remainder along (kernel form REST) where that
-// leaves the other full slices in as many launches: a row is then read at once, its line
-// at the seam and its index once.  For matrices beyond the caches (at least 2^20
-// non-zeros): uniform, 239,000 rows of 300 floats, 957 us as 64 + 11 float4, 878 so;
-// 380 floats 1086 and 1065.
+// With `join` the last full slice takes a remainder of at most kJoinF4 float4 along (kernel
+// form REST) where that leaves the other full slices in as many launches: a row is then
+// read at once, its line at the seam and its index once.  For matrices of at least 2^20
+// non-zeros; in two launches over joined, forward: uniform, 239,000 rows, 264 floats 1.13,
+// 300 floats 1.08, 352 floats 1.02, 416 floats 1.02; power law, 100,000 rows, 264 floats
+// 1.13, 300 floats 1.02, 352 floats 0.96, 416 floats 0.93, 480 floats 0.95 (a wide
+// remainder's loads in the caches wait for the slice's).
+constexpr int kJoinF4 = 12;
 static int col_launches(int f4, ColLaunch *out, int max_out, bool join) {
   const int W = slice_width();
   int n = 0;
@@ -689,7 +692,7 @@ static int col_launches(int f4, ColLaunch *out, int max_out, bool join) {
   }
   if (f4 > full && n == max_out) return -1;
   const int rem = f4 - full;
-  if (join && W == 64 && rem > 0 && n > 0 && out[n - 1].S <= 2) {
+  if (join && W == 64 && rem > 0 && rem <= kJoinF4 && n > 0 && out[n - 1].S <= 2) {
     ColLaunch &last = out[n - 1];
     if (last.S == 1) {
       last.cnt += rem;

@@ -168,10 +168,11 @@ def test_default_plans_by_width_and_alignment(f, shift, same):
     assert torch.all((outs[0] - outs[1]).abs() <= 2 * (deg + 8) * U * 6)
 
 
-@pytest.mark.parametrize("f", [257, 300, 380, 440, 600])
+@pytest.mark.parametrize("f", [257, 300, 304, 308, 380, 440, 557, 600])
 def test_row_sums_with_the_remainder_joined(f):
     """The plain kernel on a matrix of over 2^20 non-zeros: the last full slice of 64 float4 takes
-    the row's remainder along (600 floats: after a launch of one full slice)."""
+    the row's remainder of up to 12 float4 along (557 floats: after a launch of one full slice;
+    308, 380, 440 and 600: in a launch of its own)."""
     n_g, rowptr, col, owner = random_partition_graph(9000, 4000, 3, 150, 31, hub_deg=3000)
     env = {"PGCN_AGG_SLICED": "0", "PGCN_HUB": "0"}
     part = setup(env, n_g, rowptr, col, owner, 3)
