@@ -65,8 +65,8 @@ struct FwdSums {
   bool scratch;
 };
 FwdSums fwd_sums(const pgcn_partition *p, int32_t f_in, int32_t f_out, int32_t gemm_dtype, int64_t ld_in, int64_t ld_out,
-                 const float *in, const float *in_bd, const uint16_t *in16, const float *agg_lo, const float *agg_hi,
-                 int64_t ld_agg, float *A, const uint16_t *A16, float *H_out, float *acc) {
+                 const float *in, const float *in_bd, const uint16_t *in16, const float *W, int64_t w_rows,
+                 const float *agg_lo, const float *agg_hi, int64_t ld_agg, float *A, const uint16_t *A16, float *H_out, float *acc) {
   const Plan &plain = plain_plan(p, false, f_in), &pl = agg_plan(p, false, f_in, agg_lo, agg_hi, ld_agg);
   if (A) return FwdSums{&pl, A, ld_in, false};
   if (!one_pass(plain)) return FwdSums{&pl, acc, ld4(f_in), true};
@@ -74,7 +74,7 @@ FwdSums fwd_sums(const pgcn_partition *p, int32_t f_in, int32_t f_out, int32_t g
   const size_t n = (size_t)p->n_inner, h = n * (size_t)ld_out * 4, x = n * (size_t)ld_in * 4;
   if (gemm_dtype == PGCN_BF16 && f_out >= ld4(f_in) && aligned16(H_out) && !overlap(H_out, h, in, x) &&
       !overlap(H_out, h, in_bd, (size_t)p->n_bd * (size_t)ld_in * 4) && !overlap(H_out, h, in16, x / 2) &&
-      !overlap(H_out, h, A16, x / 2))
+      !overlap(H_out, h, A16, x / 2) && !overlap(H_out, h, W, (size_t)w_rows * (size_t)f_out * 4))
     return FwdSums{&pl, H_out, ld_out, true};
   return FwdSums{&plain, nullptr, ld_in, false};
 }
@@ -426,8 +426,8 @@ extern "C" int pgcn_layer_fwd(const pgcn_partition *p, const pgcn_fwd_args *a, h
     ld_agg = lds;
   }
   AggArgs g{};
-  const FwdSums sums = fwd_sums(p, a->f_in, a->f_out, a->gemm_dtype, a->ld_in, a->ld_out, a->H_in, a->H_bd, nullptr, in_lo,
-                                in_hi, ld_agg, a->A, a->A_bf16, a->H_out,
+  const FwdSums sums = fwd_sums(p, a->f_in, a->f_out, a->gemm_dtype, a->ld_in, a->ld_out, a->H_in, a->H_bd, nullptr, a->W,
+                                a->f_in, in_lo, in_hi, ld_agg, a->A, a->A_bf16, a->H_out,
                                 (float *)((char *)a->workspace + fwd_part_bytes(p, a->f_in)));
   g.plan = sums.plan;
   g.col = p->d_col;
@@ -844,7 +844,7 @@ extern "C" int pgcn_sage_layer_fwd(const pgcn_partition *p, const pgcn_sage_fwd_
   AggArgs g{};
   const float *x_bd = p->n_bd > 0 ? a->X_bd : nullptr;
   const FwdSums sums = fwd_sums(p, a->f_in, a->f_out, a->gemm_dtype, a->ld_in, a->ld_out, a->X_in, a->X_bd,
-                                a->X_in_bf16, a->X_in, x_bd, a->ld_in, a->A, a->A_bf16, a->H_out,
+                                a->X_in_bf16, a->W, 2 * (int64_t)a->f_in, a->X_in, x_bd, a->ld_in, a->A, a->A_bf16, a->H_out,
                                 (float *)((char *)a->workspace + fwd_part_bytes(p, a->f_in)));
   g.plan = sums.plan;
   g.col = p->d_col;

@@ -211,7 +211,13 @@ def test_bf16_without_fp32_aggregate_partial_slices(f_in, f_out):
     check_bf16_without_fp32_aggregate(f_in, f_out, False)
 
 
-def check_bf16_without_fp32_aggregate(f_in, f_out, in_place):
+def test_bf16_weights_inside_h_out():
+    """H_out may be the memory that holds W, which is packed before H_out is written: no running sums
+    go there (the plain plan, bit for bit)."""
+    check_bf16_without_fp32_aggregate(128, 128, False, w_inside=True)
+
+
+def check_bf16_without_fp32_aggregate(f_in, f_out, in_place, w_inside=False):
     """One plain chunk and no dense block: the plain plan keeps no running sum, and a sliced one
     keeps it in H_out where a row of it holds one of A and H_out is no input (72 -> 64, 100 ->
     64, 256 -> 128 and in place: the plain plan, bit for bit).  The workspace that the plain plan
@@ -231,11 +237,15 @@ def check_bf16_without_fp32_aggregate(f_in, f_out, in_place):
         A16 = torch.zeros((n, ld_of(f_in)), dtype=torch.bfloat16, device="cuda")
         H_in = dev(X[:n])
         H = H_in if in_place else torch.full((n, ld_of(f_out)), 5.0, device="cuda")
+        W_in = W
+        if w_inside:
+            W_in = H.view(-1)[64:64 + W.numel()]
+            W_in.copy_(W.view(-1))
         B.pgcn_layer_fwd(part, f_in=f_in, f_out=f_out, gemm_dtype=B.PGCN_BF16, relu=True, ld_in=ld_of(f_in),
-                         ld_out=ld_of(f_out), H_in=H_in, H_bd=dev(X[n:]), W=W, A=None, A_bf16=A16, H_out=H,
+                         ld_out=ld_of(f_out), H_in=H_in, H_bd=dev(X[n:]), W=W_in, A=None, A_bf16=A16, H_out=H,
                          workspace=torch.empty(nb, dtype=torch.uint8, device="cuda"), workspace_bytes=nb)
         outs.append((A16, H))
-    if in_place or f_out < (f_in + 3) // 4 * 4:
+    if in_place or w_inside or f_out < (f_in + 3) // 4 * 4:
         assert torch.equal(outs[0][0], outs[1][0]) and torch.equal(outs[0][1], outs[1][1])
         return sizes, info
     assert torch.equal(outs[1][1][:, f_out:], outs[0][1][:, f_out:])        # H_out's padding is left alone
