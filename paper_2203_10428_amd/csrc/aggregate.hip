@@ -25,7 +25,7 @@
 //    few times anyway).  Chunk c adds its partial sum to the output in chunk
 //    order; the last chunk applies the row scale.
 //  * Sliced plans (below, agg_slice_kernel) cut rows and chunks smaller, so that an
-//    XCD's L2 serves nearly every load; the rest of this list is the plain kernel.
+//    XCD's L2 serves more of the loads; the rest of this list is the plain kernel.
 //  * Long runs: one wave owns one work item (a row's run of non-zeros inside
 //    a chunk): G = 64 / SL lane groups take non-zeros k, k+1, ..., k+G-1, U
 //    of them per group in flight (masked at the row's end), then the groups
@@ -294,10 +294,12 @@ __global__ __launch_bounds__(256) void agg_kernel(AggParams p) {
 // ------------------------------------------------------ L2-resident slices ---
 //
 // Plans with Plan::sliced set: rows are cut into slices of kSliceF4 = 16 float4 (256
-// bytes) and chunks are small enough that a chunk's rows of one slice fit an XCD's
-// 4 MB L2; workgroup b takes slice b % S, so (dealt round robin) an XCD gathers from
-// one slice only and nearly every load hits its L2.  What bounds it is then the CU's
-// load path.  Each of the wave's four 16-lane groups owns one item, so nothing is
+// bytes) and, where rows are long enough, chunks are small enough that a chunk's rows of
+// one slice fit an XCD's 4 MB L2; workgroup b takes slice b % S, so (dealt round robin)
+// an XCD gathers from one slice only.  On the Reddit-like step its L2 then serves 0.92 of
+// the requests (0.72 in full slices) and the CU's load path bounds it (texture data
+// busy 0.90); short rows keep one chunk a side and hit less (products-like 0.26, where
+// full slices of the other layers hit 0.13).  Each of the wave's four 16-lane groups owns one item, so nothing is
 // added across lanes; items are sorted by length, so the groups end together.
 // Per step a group adds 8 rows, their loads in flight together: one index load per
 // 16 rows and group, one DPP row broadcast per row.  Rows are read through a buffer
@@ -305,7 +307,7 @@ __global__ __launch_bounds__(256) void agg_kernel(AggParams p) {
 // offset outside it, which reads as zero without a branch.
 // Measured on MI355X, 256-wide rows, no dense block: Reddit-like forward (88,000
 // columns, 28.9M non-zeros) 1466 us in full 64-float4 slices and 11 chunks, 1270 us
-// here in 8; half a Reddit-like transposed 619 -> 538 us (27 TB/s of gathered rows).
+// here in 8 (23 TB/s of gathered rows); half a Reddit-like transposed 619 -> 538 us (27).
 // Whole layers, dense block included: Reddit-like forward 1523 -> 1339 us, half of it
 // backward 670 -> 593 us, R-MAT of 400,000 rows forward 2050 -> 1741 us.
 // The 16 channels of an L2 interleave by 128-byte lines: where the row stride is an

@@ -19,7 +19,8 @@
 // fp32 GEMMs run by parts on the bf16 matrix cores (gemm_nk_f32s) unless
 // PGCN_GEMM_F32=native selects the fp32 matrix-core kernel (gemm_nk_f32).
 //
-// Main loop for CDNA4: a 256-thread workgroup (4 wave64s, 2 x 2) computes a
+// Main loop of gemm_nk_f32 and gemm_nk_bf16 (gemm_nk_f32s, by parts, has its own layout,
+// described there): a 256-thread workgroup (4 wave64s, 2 x 2) computes a
 // 128 x BN tile; both tiles sit in LDS with k contiguous (rows of four
 // 16-byte groups, XOR-swizzled by row so that staging writes and fragment
 // reads are free of bank conflicts) and are double buffered, so one barrier
@@ -394,11 +395,12 @@ __global__ __launch_bounds__(256, 4) void gemm_nk_f32(NKParams p) {
 // rows and all BN columns, so each activation is split once, by the lane that
 // multiplies it, in registers.  Both double buffered: 64 KB and two workgroups per CU
 // for 128 x 256 tiles, 40 KB and three for 128 x 128.
-// What bounds it at large M is the matrix cores: 1.0 PFLOP/s of bf16 products on the
-// Yelp-like feature gradient, where a plain library bf16 product of 8192^3 reaches 1.1.
-// At the smaller ones it was the activations' latency and their uncoalesced loads (a
-// row's 64 bytes on two lanes); they are now loaded two slabs ahead, a row on four
-// lanes.  Per launch, before (activation planes in LDS, 64 x 128 per wave, one slab
+// At large M the Yelp-like feature gradient runs 1.04 PFLOP/s of bf16 part products (a
+// plain library bf16 product of 8192^3: 1.1) with the matrix cores busy 0.49 of the time
+// and waves waiting on a load, an LDS read or a product 0.61 of theirs: the chain of a
+// slab, not the matrix cores, bounds it.  At the smaller ones it was the activations'
+// latency and their uncoalesced loads (a row's 64 bytes on two lanes); they are now
+// loaded two slabs ahead, a row on four lanes.  Per launch, before (activation planes in LDS, 64 x 128 per wave, one slab
 // ahead) and now: 58,000 x 256 x 256 81 -> 78 us, 14,500 x 256 x 256 43 -> 38.
 // One slab ahead for the masked operand, which brings two streams anyway, and for
 // 64-wide tiles: with two, the second register set costs the masked kernels a slab of

@@ -98,7 +98,11 @@ static int32_t choose_chunks(int64_t nrows, int64_t ncols, int64_t nnz, bool tra
 // there (the block's columns are the most referenced rows, mostly served by
 // the L2, so they cost the gather less than its average non-zero), and the
 // block costs 1.6-2.4 ps per pair.  A sweep of this constant on the
-// Reddit-like partition (0.02 to 0.08) put the best step at 0.057.
+// Reddit-like partition (0.02 to 0.08) put the best step at 0.057.  That was over the plain
+// gather; with sliced plans, 256 floats, no block and block: Reddit-like forward 1342 and
+// 1233 us, transposed 1290 and 1186, a quarter of it 310 and 271, 298 and 257, R-MAT of
+// 400,000 rows 1460 and 1413, 1353 and 1331.  Narrow rows of 41 floats: Reddit-like 418 and
+// 395, a quarter 104 and 116, R-MAT 370 and 393.
 constexpr double kHubPairCost = 0.057;
 
 static int64_t env_int(const char *name, int64_t dflt) {
