@@ -293,7 +293,7 @@ __global__ __launch_bounds__(256) void agg_kernel(AggParams p) {
 
 // ------------------------------------------------------ L2-resident slices ---
 //
-// Plans with Plan::sliced set: rows are cut into slices of kSliceF4 = 16 float4 (256
+// Plans with Plan::sliced: rows are cut into slices of kSliceF4 = 16 float4 (256
 // bytes) and, where rows are long enough, chunks are small enough that a chunk's rows of
 // one slice fit an XCD's 4 MB L2; workgroup b takes slice b % S, so (dealt round robin)
 // an XCD gathers from one slice only.  On the Reddit-like step its L2 then serves 0.92 of
@@ -677,7 +677,8 @@ static int slice_width() {
 // non-zeros; in two launches over joined, forward: uniform, 239,000 rows, 264 floats 1.13,
 // 300 floats 1.08, 352 floats 1.02, 416 floats 1.02; power law, 100,000 rows, 264 floats
 // 1.13, 300 floats 1.02, 352 floats 0.96, 416 floats 0.93, 480 floats 0.95 (a wide
-// remainder's loads in the caches wait for the slice's).
+// remainder's loads in the caches wait for the slice's).  Rows of whole 128-byte lines
+// have no line at the seam and stay apart (R-MAT, 209,000 rows, 288 floats 0.94).
 constexpr int kJoinF4 = 12;
 static int col_launches(int f4, ColLaunch *out, int max_out, bool join) {
   const int W = slice_width();
@@ -784,9 +785,9 @@ int launch_aggregate(const AggArgs &a, hipStream_t s) {
   const int f4 = (a.f + 3) / 4;
   const int C = plan.chunks;
   if (f4 > kMaxAggF4) return set_error(PGCN_EINVAL, "aggregation: feature widths above 63,740 are not supported");
-  const bool sliced = plan.sliced != SLICE_NONE;
+  const bool sliced = plan.sliced;
   ColLaunch cl[256];
-  const int ncl = sliced ? slice_launches(f4, cl, 256) : col_launches(f4, cl, 128, plan.nnz >= (int64_t)1 << 20);
+  const int ncl = sliced ? slice_launches(f4, cl, 256) : col_launches(f4, cl, 128, plan.nnz >= (int64_t)1 << 20 && a.ld_in % 32 != 0);
   if (ncl < 0) return set_error(PGCN_EINVAL, "aggregation: too many column launches");
   if (hub.rows > 0) {                      // block sums first: the rows' items add onto them
     TraceScope ts(a.trace_kind, s);

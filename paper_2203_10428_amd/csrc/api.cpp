@@ -31,10 +31,8 @@ int64_t ld4(int64_t f) { return (f + 3) / 4 * 4; }
 // only cost their writes (backward of 32,000 rows without edges, 128 -> 600 in bf16: 89 us at
 // a stride of 128, 98 at 160).
 int64_t ldw(const pgcn_partition *p, bool transposed, int64_t f) {
-  const Plan &sl = transposed ? p->plan_ts : p->plan_s;
   const int64_t lines = ((f + 31) / 32 | 1) * 32;
-  return slice_width_ok(sl, f) && (p->n_inner + (transposed ? 0 : p->n_bd)) * lines * 4 >= sl.slice_min_bytes
-             ? lines : (f + 7) / 8 * 8;
+  return slice_taken(transposed ? p->plan_ts : p->plan_s, f, source_bytes(p, transposed, lines)) ? lines : (f + 7) / 8 * 8;
 }
 
 // Stride of a workspace matrix of all n_inner + n_bd rows: ldw's, but a multiple of 8 where the

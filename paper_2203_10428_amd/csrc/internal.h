@@ -56,9 +56,13 @@ struct Hub {
   uint32_t *d_bits = nullptr, *d_init = nullptr;
 };
 
-// Widths of gathered rows for which a sliced plan is taken: none (a plain plan), whole launches of
-// 256 floats, widths that fill the slices, every width above kNarrowRow (PGCN_AGG_SLICED=1).
-enum SliceUse { SLICE_NONE, SLICE_WHOLE, SLICE_FULL, SLICE_ALL };
+// When an aggregation takes the sliced plan: for multiples of 256 floats from whole_bytes of
+// sources on, for other widths that fill the slices from full_bytes on (kNever: not at all).
+constexpr int64_t kNever = INT64_MAX;
+struct SliceUse {
+  int64_t whole_bytes = kNever, full_bytes = kNever;
+  bool always = false;          // every width above kNarrowRow (PGCN_AGG_SLICED=1)
+};
 
 struct Plan {
   int32_t chunks = 1;
@@ -67,9 +71,8 @@ struct Plan {
   std::vector<int64_t> chunk_items, chunk_whole;
   std::vector<int64_t> chunk_cols;  // chunk c holds columns [chunk_cols[c], chunk_cols[c + 1])
   int64_t ncols = 0, nnz = 0;   // columns of the matrix, entries of the array the items index
-  // a plan cut for the sliced kernel (every chunk reads one source matrix): the widths it is taken for
-  SliceUse sliced = SLICE_NONE;
-  int64_t slice_min_bytes = 0;  // ... and the size of the sources from which on it is
+  bool sliced = false;          // cut for the sliced kernel: every chunk reads one source matrix
+  SliceUse use;                 // sliced plans: the calls that take it
   int64_t slots = 0;            // partial slots of all split rows
   WorkItem *d_items = nullptr;
   SplitRow *d_splits = nullptr;
@@ -130,20 +133,25 @@ inline int64_t slice_bytes(int64_t rows, int64_t ld, int64_t f4, int64_t c4) {
   return b < (int64_t)kSliceNowhere ? b - 16 * c4 : -1;
 }
 
-// Whether a sliced plan is taken for rows of f floats.  Where the last slice leaves lanes idle,
-// and in launches of one slice, the plain kernel is the faster one.  Aggregations on MI355X,
-// plain over sliced time of the transposed plan (half a Reddit-like, half a products-like, R-MAT
-// and uniform graph): 96 floats (2 slices, 1/4 idle) 0.94, 0.85, 0.96, 0.81; 128 (2) 1.01, 1.09,
-// 1.18, 1.01; 144 (3, 1/4 idle) 0.85, 0.95, 1.12, 0.83; 192 (3) 0.87, 1.13, 1.28, 0.96; 240 (4)
-// 1.19, 1.28, 1.33, 1.02; 256 (4) 1.22, 1.21, 1.32, 1.01; 300 (5) 1.12, 1.27, 1.30, 1.02; 416 (7)
-// 1.02, 1.14, 1.25, 0.92; 512 (8) 1.18, 1.28, 1.28, 1.02.  So: 2 slices or at least 4, 7 of 8
-// lanes busy, and where an L2 holds little of a chunk (SLICE_WHOLE) multiples of 256 floats.
-inline bool slice_width_ok(const Plan &plan, int64_t f) {
+// Whether a sliced plan is taken for rows of f floats from sources of `bytes` bytes.  Where the
+// last slice leaves lanes idle, and in launches of one slice, the plain kernel is the faster one.
+// Aggregations on MI355X, plain over sliced time of the transposed plan (half a Reddit-like, half
+// a products-like, R-MAT and uniform graph): 96 floats (2 slices, 1/4 idle) 0.94, 0.85, 0.96,
+// 0.81; 128 (2) 1.01, 1.09, 1.18, 1.01; 144 (3, 1/4 idle) 0.85, 0.95, 1.12, 0.83; 192 (3) 0.87,
+// 1.13, 1.28, 0.96; 240 (4) 1.19, 1.28, 1.33, 1.02; 256 (4) 1.22, 1.21, 1.32, 1.01; 300 (5) 1.12,
+// 1.27, 1.30, 1.02; 416 (7) 1.02, 1.14, 1.25, 0.92; 512 (8) 1.18, 1.28, 1.28, 1.02.  So: 2 slices
+// or at least 4, 7 of 8 lanes busy; multiples of 256 floats, which fill whole launches, gain
+// the most and on more graphs.
+inline bool slice_taken(const Plan &plan, int64_t f, int64_t bytes) {
   const int64_t f4 = (f + 3) / 4, slices = (f4 + kSliceF4 - 1) / kSliceF4;
-  if (f <= kNarrowRow || plan.sliced == SLICE_NONE) return false;
-  if (plan.sliced == SLICE_ALL) return true;
-  if (plan.sliced == SLICE_WHOLE) return f4 % (4 * kSliceF4) == 0;
-  return (slices == 2 || slices >= 4) && 8 * f4 >= 7 * slices * kSliceF4;
+  if (f <= kNarrowRow || !plan.sliced) return false;
+  if (plan.use.always || (f4 % (4 * kSliceF4) == 0 && bytes >= plan.use.whole_bytes)) return true;
+  return (slices == 2 || slices >= 4) && 8 * f4 >= 7 * slices * kSliceF4 && bytes >= plan.use.full_bytes;
+}
+
+// Bytes of the sources of an aggregation with a row stride of ld floats.
+inline int64_t source_bytes(const pgcn_partition *p, bool transposed, int64_t ld) {
+  return (p->n_inner + (transposed ? 0 : p->n_bd)) * ld * 4;
 }
 
 // The plain work plan for an aggregation of P_i (transposed: P_i^T) over rows of f floats.
@@ -162,14 +170,13 @@ inline const Plan &plain_plan(const pgcn_partition *p, bool transposed, int64_t 
 inline const Plan &agg_plan(const pgcn_partition *p, bool transposed, int64_t f, const float *lo, const float *hi,
                             int64_t ld) {
   const Plan &sl = transposed ? p->plan_ts : p->plan_s, &plain = plain_plan(p, transposed, f);
-  if (!slice_width_ok(sl, f)) return plain;
+  if (!slice_taken(sl, f, source_bytes(p, transposed, ld))) return plain;
   const int64_t f4 = (f + 3) / 4, n_hi = transposed || !hi ? 0 : p->n_bd;
   if (slice_bytes(lo ? p->n_inner : 0, ld, f4, 0) < 0 || slice_bytes(n_hi, ld, f4, 0) < 0 ||
       sl.nnz >= (int64_t)kSliceNowhere / 4 - 64)
     return plain;
-  if (sl.sliced == SLICE_ALL) return sl;
-  if (ld % 32 != 0 || (((uintptr_t)lo | (uintptr_t)hi) & 127u) != 0) return plain;
-  return (p->n_inner + (transposed ? 0 : p->n_bd)) * ld * 4 >= sl.slice_min_bytes ? sl : plain;
+  if (sl.use.always) return sl;
+  return ld % 32 != 0 || (((uintptr_t)lo | (uintptr_t)hi) & 127u) != 0 ? plain : sl;
 }
 
 int set_error(int code, const std::string &msg) noexcept;

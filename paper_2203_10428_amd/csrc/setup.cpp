@@ -260,28 +260,34 @@ constexpr int64_t kSliceL2Rows = 12288;
 // Column cuts of a sliced plan (kernel agg_slice_kernel), empty where no width is the better for
 // one.  Columns [0, split) and [split, ncols) come from two matrices and are cut apart; each
 // side takes chunks of about kSliceChunkRows, while a row keeps >= 32 non-zeros per chunk.
-// Sets which widths take the plan (`use`, slice_width_ok) and, in bytes of the sources, from
-// where on (`min_bytes`).  Worth it (measured on MI355X) where the slices raise the share of
-// gathers that an L2 serves:
+// `use` is set to the calls that take the plan.  Measured on MI355X, plain over sliced time:
 //  * not below 2^20 non-zeros or 4,096 columns (whole 1 KB rows fit an L2 there);
-//  * where the kSliceL2Rows most referenced columns of each chunk hold >= a quarter of its
-//    non-zeros.  Below that only the transposed plans gain, a little and in whole launches:
-//    uniform, 239,000 rows (0.12 of them held), plain over sliced time 1.01 at 256 and 512
-//    floats, 0.90 to 0.99 at 224, 288 and 416; forward 512 floats 1440 -> 1588 us;
-//  * a chunk more than the plain plan's moves each output row twice, for runs that are
-//    shorter by as much: with under 24 non-zeros a run, and sources that the 256 MB last-level
-//    cache serves, the forward is slower sliced.  Plain over sliced time at 128, 256, 384
-//    and 512 floats: R-MAT of 144,000 source rows (runs of 15) 0.74, 0.96, 0.84, 1.05, power
-//    law of 165,000 (15) 0.75, 1.05, 0.96, 1.12; R-MAT of 567,000 (17) 1.28, 1.26, 1.29, 1.19,
-//    products-like of 228,000 (25) 1.11, 1.19, 1.16, 1.18.  Hence 400 MB below 24.
+//  * the slices have to raise the share of gathers that an L2 serves: the kSliceL2Rows most
+//    referenced columns of each chunk hold >= a quarter of its non-zeros.  Below that only
+//    transposed plans gain, in whole launches: uniform, 239,000 rows (0.12 of them held), 1.01
+//    at 256 and 512 floats, 0.90 to 0.99 at 224, 288 and 416; forward 1440 -> 1588 us at 512;
+//  * a run (of non-zeros outside the dense block) takes 16 lanes, however short.  Transposed (one chunk, as in the plain plan), at 128,
+//    256, 288, 416 and 512 floats: runs of 9 (power law, 80,000 source rows) 0.78, 1.05, 0.85,
+//    0.82, 1.11, of 16 (60,000) 0.82, 1.13, 0.88, 0.85, 1.23, of 22 (40,000) 0.89, 1.22, 0.94,
+//    0.91, 1.37; of 24 (hubs, 40,000) 1.21, 1.30, 1.09, 1.12, 1.28; beyond the caches of 12
+//    (power law, 200,000) 1.02, 1.09, 0.98, 1.00, 1.09, of 15 (R-MAT, 200,000) 1.17, 1.27, 1.11,
+//    1.16, 1.22.  So from 24 on, from 12 on with sources of 128 MB, else from 400 MB, and
+//    multiples of 256 floats anyway;
+//  * a chunk more than the plain plan's moves each output row twice, and halves the runs.
+//    Forward at the same widths: runs of 5 (power law, 266,000 source rows) 0.54 at 416, 0.85 at
+//    512, of 10 (330,000) 0.83, 0.95, of 11 (R-MAT, 281,000) 0.97 and 1.13, of 12 (R-MAT,
+//    144,000) 0.74, 0.96, 0.76, 0.71, 1.05, of 15 (power law, 165,000) 0.75, 1.05, 0.81, 0.81,
+//    1.12, of 15 (R-MAT, 567,000) 1.28, 1.26, 1.21, 1.25, 1.19, of 25 (products-like, 228,000)
+//    1.11, 1.19, 1.05, 1.05, 1.18, of 30 (power law, 46,000) 0.74, 1.29, 0.88, 0.84, 1.70.  So
+//    from 24 on with sources of 96 MB or multiples of 256 floats, from 14 on from 400 MB, else
+//    not.
 // PGCN_AGG_SLICED=0 / 1 (environment) never / always cuts so, for every width above kNarrowRow;
 // a chunk count given by PGCN_AGG_CHUNKS or PGCN_AGG_CHUNKS_T is the plain plans' (with
 // PGCN_AGG_SLICED=1, the total over both sides).
 static std::vector<int64_t> choose_slices(const std::vector<int64_t> &rowptr, const std::vector<int32_t> &col,
                                           int64_t nrows, int64_t ncols, int64_t split, bool transposed,
-                                          int32_t plain_chunks, SliceUse &use, int64_t &min_bytes) {
-  use = SLICE_NONE;
-  min_bytes = 0;
+                                          int32_t plain_chunks, SliceUse &use) {
+  use = SliceUse();
   const char *env = std::getenv("PGCN_AGG_SLICED");
   const bool forced = env && std::strcmp(env, "1") == 0;
   const int64_t nnz = (int64_t)col.size();
@@ -303,7 +309,7 @@ static std::vector<int64_t> choose_slices(const std::vector<int64_t> &rowptr, co
   for (int64_t c = 0; c < chi; ++c) cuts.push_back(split + (ncols - split) * c / chi);
   cuts.push_back(ncols);
   if (forced) {
-    use = SLICE_ALL;
+    use.always = true;
     return cuts;
   }
   int64_t held = 0;
@@ -317,13 +323,20 @@ static std::vector<int64_t> choose_slices(const std::vector<int64_t> &rowptr, co
   }
   // every chunk more than the plain plan's moves each output row twice: the gathers it has to save
   const int64_t chunks = (int64_t)cuts.size() - 1, moved = 2 * nrows * std::max<int64_t>(0, chunks - plain_chunks);
-  if (4 * (held - moved) >= nnz) {
-    use = SLICE_FULL;
-    if (chunks > plain_chunks && nnz < 24 * nrows * chunks) min_bytes = (int64_t)400 << 20;
-  } else if (transposed && chunks <= plain_chunks) {
-    use = SLICE_WHOLE;
+  const int64_t rows = nrows * chunks;                   // runs of nnz / rows non-zeros
+  constexpr int64_t MB = (int64_t)1 << 20;
+  if (4 * (held - moved) < nnz) {
+    if (transposed && chunks <= plain_chunks) use.whole_bytes = 0;
+  } else if (chunks <= plain_chunks) {
+    use.whole_bytes = 0;
+    use.full_bytes = nnz >= 24 * rows ? 0 : nnz >= 12 * rows ? 128 * MB : 400 * MB;
+  } else if (nnz >= 24 * rows) {
+    use.whole_bytes = 0;
+    use.full_bytes = 96 * MB;
+  } else if (nnz >= 14 * rows) {
+    use.whole_bytes = use.full_bytes = 400 * MB;
   }
-  return use == SLICE_NONE ? std::vector<int64_t>{} : cuts;
+  return use.whole_bytes == kNever ? std::vector<int64_t>{} : cuts;
 }
 
 // Work plan of one aggregation over the column chunks `cuts`.  A row whose run inside
@@ -705,7 +718,8 @@ extern "C" int pgcn_partition_setup(const pgcn_csr *csr, const pgcn_boundary_map
         share_hub(plan, nar);
       }
       const std::vector<int64_t> cuts =
-          choose_slices(rp, cl, nrows, ncols, n_in, transposed, chunks, sl.sliced, sl.slice_min_bytes);
+          choose_slices(rp, cl, nrows, ncols, n_in, transposed, chunks, sl.use);
+      sl.sliced = !cuts.empty();
       if (cuts.empty()) return;
       int64_t segment = 2 * (int64_t)p->segment;
       while (plan_slots(rp, cl, nrows, cuts, segment) > plan.slots) segment *= 2;

@@ -73,7 +73,7 @@ def test_rows_packed_by_inner_row(probe, f, ld, dst, most):
 # ------------------------------------------------------------- sliced plans ---
 
 PLAIN, NARROW, SLICED = range(3)
-NONE, WHOLE, FULL, ALL = range(4)
+NEVER, MB = -1, 1 << 20
 AT = 1 << 20                                             # an address of whole lines
 
 
@@ -87,7 +87,7 @@ def clean(monkeypatch):
 def plan(probe, part, transposed, which):
     out = (_i64 * 256)()
     n = probe.probe_plan(part.handle, transposed, which, out)
-    return dict(zip(("chunks", "slots", "use", "min_bytes"), out[:4]), cuts=list(out[4:n]))
+    return dict(zip(("chunks", "slots", "whole", "full"), out[:4]), cuts=list(out[4:n]))
 
 
 def skewed_graph(n_inner, n_pool, m, seed, columns):
@@ -108,23 +108,27 @@ def uniform_graph(n_inner, n_pool, deg):
 
 @pytest.mark.parametrize("graph,forward,transposed", [
     # below 2^20 non-zeros: plain plans
-    (lambda: uniform_graph(8000, 4500, 100), NONE, NONE),
-    # dense enough that whole chunks stay in an L2
-    (lambda: uniform_graph(9000, 4500, 140), FULL, FULL),
-    # sparse: an L2 holds a tenth of the gathers of a uniform graph, most of a skewed one's
-    (lambda: uniform_graph(120000, 60000, 11), NONE, WHOLE),
-    (lambda: skewed_graph(60000, 30000, 700000, 5, 2000), FULL, FULL)])
+    (lambda: uniform_graph(8000, 4500, 100), (NEVER, NEVER), (NEVER, NEVER)),
+    # long runs, whole chunks stay in an L2, no more chunks than the plain plan's
+    (lambda: uniform_graph(9000, 4500, 140), (0, 0), (0, 0)),
+    # an L2 holds a tenth of the gathers of a sparse uniform graph: whole launches of the transposed plan
+    (lambda: uniform_graph(120000, 60000, 11), (NEVER, NEVER), (0, NEVER)),
+    # skewed, short runs in one chunk a side, two in the forward plan: 6 to 7, 14 to 15, 27 non-zeros a run there
+    (lambda: skewed_graph(120000, 60000, 900000, 5, 2000), (NEVER, NEVER), (0, 400 * MB)),
+    (lambda: skewed_graph(60000, 30000, 1020000, 5, 2000), (400 * MB, 400 * MB), (0, 128 * MB)),
+    (lambda: skewed_graph(30000, 15000, 1000000, 5, 2000), (0, 96 * MB), (0, 0))])
 def test_default_choice_of_sliced_plans(probe, clean, graph, forward, transposed):
     n, rowptr, col, owner = graph()
+    clean.setenv("PGCN_HUB", "0")                        # a dense block would take non-zeros off the runs
     part = B.pgcn_partition_setup(n, rowptr, col, owner, 2, 0, host_only=True)
     info = B.pgcn_partition_info(part)
     n_in, n_bd, nnz = info["n_inner"], info["n_bd"], info["nnz"]
-    assert (nnz >= 1 << 20) == (transposed != NONE) and max(n_in, n_bd) > 4096
+    assert (nnz >= 1 << 20) == (transposed != (NEVER, NEVER)) and max(n_in, n_bd) > 4096
     for t, use, nrows, sides in ((0, forward, n_in, (n_in, n_bd)), (1, transposed, n_in + n_bd, (n_in,))):
         plain, sl = plan(probe, part, t, PLAIN), plan(probe, part, t, SLICED)
-        assert plain["use"] == NONE and sl["use"] == use
-        assert info["spmmt_chunks" if t else "spmm_chunks"] == (sl if use else plain)["chunks"]
-        if use == NONE:
+        assert (sl["whole"], sl["full"]) == use, (t, nnz / nrows)
+        assert info["spmmt_chunks" if t else "spmm_chunks"] == (sl if sl["chunks"] else plain)["chunks"]
+        if use == (NEVER, NEVER):
             assert sl["chunks"] == 0
             continue
         assert sl["slots"] <= plain["slots"]             # the scratch memory is sized by the plain plan
@@ -132,18 +136,19 @@ def test_default_choice_of_sliced_plans(probe, clean, graph, forward, transposed
         assert cuts[0] == 0 and cuts[-1] == sum(sides) and all(s in cuts for s in np.cumsum(sides))
         for a, b in zip(cuts, cuts[1:]):
             assert 0 < b - a and (b - a <= 16500 or nnz // nrows < 64)
-        short = len(cuts) - 1 > plain["chunks"] and nnz < 24 * nrows * (len(cuts) - 1)
-        assert sl["min_bytes"] == (400 << 20 if short else 0)
-        for f, full in ((64, 0), (65, 0), (96, 0), (112, 1), (128, 1), (144, 0), (192, 0), (200, 0), (224, 1), (256, 1),
-                        (300, 1), (512, 1), (602, 1)):
-            ld = -(-f // 32) * 32 if not short else 1 << 13
-            takes = bool(full) if use == FULL else f % 256 == 0
-            assert (probe.probe_taken(part.handle, t, f, AT, 0 if t else AT, ld) == SLICED) == takes, (t, f)
+        rows = n_in if t else n_in + n_bd
+        for f, kind in ((64, None), (65, None), (96, None), (112, "full"), (128, "full"), (144, None), (192, None),
+                        (200, None), (224, "full"), (256, "whole"), (300, "full"), (512, "whole"), (602, "full")):
+            at = sl[kind] if kind else NEVER
+            tight = -(-f // 32) * 32
+            for ld in {tight, max(tight, -(-max(at, 0) // (4 * rows * 32)) * 32), 1 << 13}:
+                taken = probe.probe_taken(part.handle, t, f, AT, 0 if t else AT, ld) == SLICED
+                assert taken == (at != NEVER and 4 * rows * ld >= at), (t, f, ld)
 
 
 def test_calls_that_leave_the_sliced_plan(probe, clean):
-    """Sources whose slices straddle lines, sources of 4 GiB and sources that the caches serve run the
-    plain plan, as narrow rows and refused widths do; PGCN_AGG_SLICED=1 keeps all but the 4 GiB ones."""
+    """Sources whose slices straddle lines and sources of 4 GiB run the plain plan, as narrow rows and
+    refused widths do; PGCN_AGG_SLICED=1 keeps all but the 4 GiB ones."""
     n, rowptr, col, owner = uniform_graph(9000, 4500, 140)
     part = B.pgcn_partition_setup(n, rowptr, col, owner, 2, 0, host_only=True)
     took = lambda f, lo, hi, ld, t=0: probe.probe_taken(part.handle, t, f, lo, hi, ld)
@@ -151,14 +156,7 @@ def test_calls_that_leave_the_sliced_plan(probe, clean):
     assert took(256, AT, AT, 260) == took(256, AT + 64, AT, 256) == took(256, AT, AT + 16, 256) == PLAIN
     limit = 0xfffff000 // 4 // 8999 // 32 * 32           # the second row of 9,000 that passes 32-bit offsets
     assert took(256, AT, AT, limit - 32) == SLICED and took(256, AT, AT, limit + 32) == PLAIN
-    n, rowptr, col, owner = skewed_graph(60000, 30000, 700000, 5, 2000)
-    part = B.pgcn_partition_setup(n, rowptr, col, owner, 2, 0, host_only=True)
-    info = B.pgcn_partition_info(part)
-    rows = info["n_inner"] + info["n_bd"]
-    least = plan(probe, part, 0, SLICED)["min_bytes"]
-    assert least == 400 << 20
-    ld = -(-(least // 4 // rows) // 32) * 32
-    assert took(256, AT, AT, ld + 32) == SLICED and took(256, AT, AT, ld - 32) == PLAIN
+    n, rowptr, col, owner = skewed_graph(60000, 30000, 1020000, 5, 2000)
     clean.setenv("PGCN_AGG_SLICED", "1")
     part = B.pgcn_partition_setup(n, rowptr, col, owner, 2, 0, host_only=True)
     for f in (65, 72, 100, 144, 300, 602):
