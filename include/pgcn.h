@@ -133,10 +133,10 @@ typedef struct pgcn_partition pgcn_partition;
  *                      kernel of L2-resident row slices, over a plan of its own (read by
  *                      pgcn_partition_setup; default: on matrices of at least 2^20
  *                      non-zeros, for widths, strides, alignments and source sizes
- *                      where that is faster, chunks of about 11,000 rows, none across the inner and
- *                      boundary rows; PGCN_AGG_CHUNKS and PGCN_AGG_CHUNKS_T give plain
- *                      plans alone unless this is 1).  Sources of 4 GiB and more always
- *                      take the plain plan;
+ *                      where that is faster, chunks of about 11,000 rows, none across
+ *                      the inner and boundary rows; PGCN_AGG_CHUNKS and
+ *                      PGCN_AGG_CHUNKS_T give plain plans alone unless this is 1).
+ *                      Sources of 4 GiB and more always take the plain plan;
  *   PGCN_SEGMENT       length at which long rows are split into segments,
  *                      16..1048576 (read by pgcn_partition_setup; default 512; at
  *                      least twice that in sliced plans);

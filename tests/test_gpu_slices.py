@@ -173,11 +173,22 @@ def test_row_sums_with_the_remainder_joined(f):
     """The plain kernel on a matrix of over 2^20 non-zeros: the last full slice of 64 float4 takes
     the row's remainder of up to 12 float4 along (557 floats: after a launch of one full slice;
     308, 380, 440 and 600: in a launch of its own)."""
+    check_joined(f, {"PGCN_HUB": "0"}, lambda d: (d + 8) * U)
+
+
+@pytest.mark.parametrize("f", [257, 300, 557])
+def test_remainder_joined_beside_a_dense_block(f):
+    """The block's sums add three parts of each term, |x| (1 + 2^-7) together at most, in fp32."""
+    check_joined(f, {"PGCN_HUB_ROWS": "600", "PGCN_HUB_COLS": "1000"}, lambda d: (3 * d + 16) * U * (1 + 2.0 ** -7))
+
+
+def check_joined(f, env, factor):
     n_g, rowptr, col, owner = random_partition_graph(9000, 4000, 3, 150, 31, hub_deg=3000)
-    env = {"PGCN_AGG_SLICED": "0", "PGCN_HUB": "0"}
+    env = {"PGCN_AGG_SLICED": "0", **env}
     part = setup(env, n_g, rowptr, col, owner, 3)
     info = B.pgcn_partition_info(part)
-    assert info["nnz"] >= 1 << 20 and info["spmm_split_slots"] > 0
+    assert info["nnz"] >= 1 << 20 and (info["spmm_hub_nnz"] > 0) == (env.get("PGCN_HUB") is None)
+    assert info["spmm_hub_nnz"] > 0 or info["spmm_split_slots"] > 0
     P = propagation_matrix(build_partition(n_g, rowptr, col, owner, 0, 3), "mean")
     n, b = info["n_inner"], info["n_bd"]
     X = np.random.default_rng(f).standard_normal((n + b, f)).astype(np.float32)
@@ -188,7 +199,7 @@ def test_row_sums_with_the_remainder_joined(f):
                      H_bd=dev(X[n:]), W=W, A=A, A_bf16=None, H_out=dev(np.zeros((n, 8))),
                      workspace=torch.empty(nb, dtype=torch.uint8, device="cuda"), workspace_bytes=nb)
     Xd, d = X.astype(np.float64), np.diff(P.indptr)[:, None]
-    assert np.all(np.abs(host(A, f) - P @ Xd) <= (d + 8) * U * (P @ np.abs(Xd)))
+    assert np.all(np.abs(host(A, f) - P @ Xd) <= factor(d) * (P @ np.abs(Xd)))
 
 
 @pytest.mark.parametrize("model,norm,order", FORMS)
